@@ -353,6 +353,10 @@ mxq_status mxq_gemm_partials(const mxq_fmt *fmt, int64_t M, int64_t N,
  *     [n_samples][K], caller-owned scratch), then are added to s in sample
  *     order, so the result equals n_samples calls of mxq_calib_colsq.
  *     n_samples in [1, 65535].
+ *   mxq_calib_colsq_list: the same for n_samples separate samples in one
+ *     launch: sample i is x[i] (HOST array of DEVICE pointers) of rows[i]
+ *     rows at a leading dimension of ldx[i] (HOST arrays, read before the
+ *     call returns).  n_samples in [1, MXQ_CALIB_LIST_MAX].
  *   mxq_calib_ratio (HOST only): Theorem A.1's control parameter
  *     R = ((B - 4) * sum d_i - 4 * 32 * n) / sum(2 * S_i * (d_i - 32)) for n
  *     layers of input widths d_in[i] (multiples of 32) and layer
@@ -381,6 +385,11 @@ mxq_status mxq_calib_colsq_samples(const uint16_t *x, int64_t n_samples,
                                    int64_t sample_stride, int64_t K,
                                    double *work, double *s, int accumulate,
                                    void *stream);
+#define MXQ_CALIB_LIST_MAX 32
+mxq_status mxq_calib_colsq_list(const uint16_t *const *x, const int64_t *rows,
+                                const int64_t *ldx, int64_t n_samples,
+                                int64_t K, double *work, double *s,
+                                int accumulate, void *stream);
 mxq_status mxq_calib_ratio(int32_t n, const int64_t *d_in,
                            const double *s_layer, double B, double *R);
 mxq_status mxq_calib_counts(int64_t d_in, double R, double s_layer,

@@ -371,6 +371,19 @@ mxq_status mxq_calib_colsq_samples(const uint16_t *x, int64_t n_samples, int64_t
                                                   work, s, accumulate != 0, (hipStream_t)stream));
 }
 
+mxq_status mxq_calib_colsq_list(const uint16_t *const *x, const int64_t *rows,
+                                const int64_t *ldx, int64_t n_samples, int64_t K, double *work,
+                                double *s, int accumulate, void *stream) {
+  if (!x || !rows || !ldx || !s || !work) return MXQ_ERR_NULL;
+  if (n_samples < 1 || n_samples > MXQ_CALIB_LIST_MAX || K <= 0) return MXQ_ERR_SHAPE;
+  for (int64_t i = 0; i < n_samples; ++i) {
+    if (!x[i]) return MXQ_ERR_NULL;
+    if (rows[i] < 0 || ldx[i] < K) return MXQ_ERR_SHAPE;
+  }
+  return launched(mxq::launch_calib_colsq_list(x, rows, ldx, n_samples, K, work, s,
+                                               accumulate != 0, (hipStream_t)stream));
+}
+
 mxq_status mxq_calib_ratio(int32_t n, const int64_t *d_in, const double *s_layer, double B,
                            double *R) {
   if (!d_in || !s_layer || !R) return MXQ_ERR_NULL;

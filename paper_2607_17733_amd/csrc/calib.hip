@@ -7,15 +7,17 @@
 // Algorithm 2: sort a layer's columns by descending sensitivity; the top 32
 // get 8-bit mantissas, the next N6 6-bit, the rest 4-bit.
 //
-// Sensitivities are float64 and computed in a fixed order, one thread per
+// Sensitivities are float64 and computed in a fixed order, one lane per
 // column: a sample's rows are summed in row order from zero (every square of
 // a bf16 value is exact in float64), and the sample's sum is then added to
-// the running total.  The sort is by counting: a column's rank is the number
-// of columns that sort before it (larger sensitivity, or equal with a lower
-// index; a NaN counts as +inf), which fixes a unique order without a
-// parallel sort.  The rank then places the column in the permutation: the
-// 4-bit columns first, then the 6-bit and the 8-bit ones, each in sorted
-// order.
+// the running total.  The row order makes each column one serial chain of
+// float64 additions, so the parallelism is columns x samples: one wave per
+// 64 columns and sample, all samples of a call in one launch.  The sort is by
+// counting: a column's rank is the number of columns that sort before it
+// (larger sensitivity, or equal with a lower index; a NaN counts as +inf),
+// which fixes a unique order without a parallel sort.  The rank then places
+// the column in the permutation: the 4-bit columns first, then the 6-bit and
+// the 8-bit ones, each in sorted order.
 #include "mxq_internal.h"
 
 namespace mxq {
@@ -23,61 +25,86 @@ namespace mxq {
 namespace {
 
 constexpr int kCalThreads = 256;
+constexpr int kColLanes = 64;       // columns of a wave
+constexpr int kRowBatch = 32;       // rows in flight while as many are summed
 
 __device__ inline double bf16_to_f64(uint16_t v) {
   return (double)__uint_as_float((uint32_t)v << 16);
 }
 
-__global__ __launch_bounds__(kCalThreads) void colsq_kernel(const uint16_t *__restrict__ x,
-                                                            int64_t rows, int64_t ld, int64_t K,
-                                                            double *s, int accumulate) {
-  const int64_t k = (int64_t)blockIdx.x * kCalThreads + threadIdx.x;
-  if (k >= K) return;
-  const uint16_t *p = x + k;
-  double part = 0.0;
-  int64_t r = 0;
-  for (; r + 8 <= rows; r += 8) {
-    uint16_t v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = p[(r + u) * ld];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const double d = bf16_to_f64(v[u]);
-      part += d * d;
-    }
-  }
-  for (; r < rows; ++r) {
-    const double d = bf16_to_f64(p[r * ld]);
-    part += d * d;
-  }
-  s[k] = accumulate ? s[k] + part : part;
+// The samples of one launch: sample i's rows start at x[i], or, for a batch
+// in one tensor, at base + i * stride.
+struct SampleList {
+  const uint16_t *x[MXQ_CALIB_LIST_MAX];
+  int64_t rows[MXQ_CALIB_LIST_MAX], ld[MXQ_CALIB_LIST_MAX];
+};
+struct SampleBatch {
+  const uint16_t *base;
+  int64_t stride, nrows, lead;
+};
+__device__ inline const uint16_t *sample_ptr(const SampleList &l, int i) { return l.x[i]; }
+__device__ inline int64_t sample_rows(const SampleList &l, int i) { return l.rows[i]; }
+__device__ inline int64_t sample_ld(const SampleList &l, int i) { return l.ld[i]; }
+__device__ inline const uint16_t *sample_ptr(const SampleBatch &b, int i) {
+  return b.base + (int64_t)i * b.stride;
 }
+__device__ inline int64_t sample_rows(const SampleBatch &b, int) { return b.nrows; }
+__device__ inline int64_t sample_ld(const SampleBatch &b, int) { return b.lead; }
 
-// Several samples at once (blockIdx.y = sample): each sample's sums, in row
-// order, go to its row of `part`; then the samples are added in order.
-__global__ __launch_bounds__(kCalThreads) void colsq_samples_kernel(
-    const uint16_t *__restrict__ x, int64_t rows, int64_t ld, int64_t sample_stride, int64_t K,
-    double *part) {
-  const int64_t k = (int64_t)blockIdx.x * kCalThreads + threadIdx.x;
+// One wave per 64 columns (blockIdx.x) and sample (blockIdx.y): the column
+// sums of the sample in row order, to its row of `out` (or added to it).
+// With the samples in one launch the kernel is bound by the HBM read; a wave
+// keeps the next 32 rows in flight while it sums the current 32 (64 loads,
+// the most a wave can count).  Sixteen samples of 2048 x 4096 (268 MB): 43.5 us
+// (6.2 TB/s); a launch per sample, whose 64 waves are a sixteenth of the
+// GPU's SIMDs, took 98 us each.
+template <class Samples>
+__global__ __launch_bounds__(kColLanes) void colsq_kernel(Samples sm, int64_t K, double *out,
+                                                          int accumulate) {
+  const int y = blockIdx.y;
+  const int64_t k = (int64_t)blockIdx.x * kColLanes + threadIdx.x;
+  const int64_t rows = sample_rows(sm, y), ld = sample_ld(sm, y);
   if (k >= K) return;
-  const uint16_t *p = x + (int64_t)blockIdx.y * sample_stride + k;
+  const uint16_t *p = sample_ptr(sm, y) + k;
   double sum = 0.0;
-  int64_t r = 0;
-  for (; r + 8 <= rows; r += 8) {
-    uint16_t v[8];
+  auto fetch = [&](uint16_t (&v)[kRowBatch], int64_t r) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = p[(r + u) * ld];
+    for (int u = 0; u < kRowBatch; ++u) v[u] = p[(r + u) * ld];
+  };
+  auto add = [&](const uint16_t (&v)[kRowBatch]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < kRowBatch; ++u) {
       const double d = bf16_to_f64(v[u]);
       sum += d * d;
     }
+  };
+  int64_t r = 0;
+  const int64_t nb = rows / kRowBatch;
+  if (nb > 0) {
+    uint16_t a[kRowBatch], b[kRowBatch];
+    fetch(a, 0);
+    int64_t i = 1;
+    for (; i + 1 < nb; i += 2) {
+      fetch(b, i * kRowBatch);
+      add(a);
+      fetch(a, (i + 1) * kRowBatch);
+      add(b);
+    }
+    if (i < nb) {
+      fetch(b, i * kRowBatch);
+      add(a);
+      add(b);
+    } else {
+      add(a);
+    }
+    r = nb * kRowBatch;
   }
   for (; r < rows; ++r) {
     const double d = bf16_to_f64(p[r * ld]);
     sum += d * d;
   }
-  part[(int64_t)blockIdx.y * K + k] = sum;
+  double *o = out + (int64_t)y * K + k;
+  *o = accumulate ? *o + sum : sum;
 }
 
 __global__ __launch_bounds__(kCalThreads) void add_samples_kernel(const double *__restrict__ part,
@@ -92,60 +119,111 @@ __global__ __launch_bounds__(kCalThreads) void add_samples_kernel(const double *
 
 __device__ inline double sort_key(double v) { return v != v ? __builtin_inf() : v; }
 
+// A workgroup ranks kRankCols columns; each wave compares 64 columns j at a
+// time with all of them.  The compare leaves a lane mask, whose population
+// count is scalar work, so a (column, 64 j) pair costs one vector
+// instruction: the rank of K columns is K^2 / 64 compares spread over
+// K / kRankCols workgroups (K = 4096: 12.4 us; one thread per column, sixteen
+// workgroups walking all K keys, took 310 us).
+constexpr int kRankCols = 16;
+
 __global__ __launch_bounds__(kCalThreads) void rank_perm_kernel(const double *__restrict__ s,
                                                                 int64_t K, int64_t n4,
                                                                 int64_t n6, int64_t n8,
                                                                 int32_t *perm) {
-  __shared__ double tile[kCalThreads];
-  const int t = threadIdx.x;
-  const int64_t i = (int64_t)blockIdx.x * kCalThreads + t;
-  const double si = i < K ? sort_key(s[i]) : 0.0;
-  int64_t before = 0;
-  for (int64_t j0 = 0; j0 < K; j0 += kCalThreads) {
-    __syncthreads();
-    if (j0 + t < K) tile[t] = sort_key(s[j0 + t]);
-    __syncthreads();
-    const int jn = (int)(K - j0 < kCalThreads ? K - j0 : kCalThreads);
-    for (int jj = 0; jj < jn; ++jj) {
-      const double sj = tile[jj];
-      before += (sj > si) || (sj == si && j0 + jj < i);
+  constexpr int kW = kCalThreads / 64;
+  __shared__ int cnt[kW][kRankCols];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i0 = (int64_t)blockIdx.x * kRankCols;
+  double key[kRankCols];
+  int before[kRankCols];
+#pragma unroll
+  for (int c = 0; c < kRankCols; ++c) {
+    key[c] = i0 + c < K ? sort_key(s[i0 + c]) : 0.0;
+    before[c] = 0;
+  }
+  // 64 columns from j0: all of them before the workgroup's columns (equal
+  // sensitivities sort first), all after, or mixed
+  for (int64_t j0 = 64 * wave; j0 < K; j0 += kCalThreads) {
+    const int64_t j = j0 + lane;
+    const bool in = j < K;
+    const double sj = in ? sort_key(s[j]) : -__builtin_inf();   // not before any column
+    if (j0 + 64 <= i0) {
+#pragma unroll
+      for (int c = 0; c < kRankCols; ++c) before[c] += __popcll(__ballot(sj >= key[c]));
+    } else if (j0 >= i0 + kRankCols) {
+#pragma unroll
+      for (int c = 0; c < kRankCols; ++c) before[c] += __popcll(__ballot(sj > key[c]));
+    } else {
+#pragma unroll
+      for (int c = 0; c < kRankCols; ++c)
+        before[c] += __popcll(__ballot(in && (sj > key[c] || (sj == key[c] && j < i0 + c))));
     }
   }
-  if (i >= K) return;
+#pragma unroll
+  for (int c = 0; c < kRankCols; ++c)
+    if (lane == 0) cnt[wave][c] = before[c];
+  __syncthreads();
+  const int64_t i = i0 + threadIdx.x;
+  if (threadIdx.x >= kRankCols || i >= K) return;
+  int64_t rank = 0;
+#pragma unroll
+  for (int w = 0; w < kW; ++w) rank += cnt[w][threadIdx.x];
   const int64_t c8 = 32 * n8, c6 = 32 * n6, c4 = 32 * n4;
   int64_t pos;
-  if (before < c8) pos = c4 + c6 + before;                   // 8-bit: the last blocks
-  else if (before < c8 + c6) pos = c4 + (before - c8);       // 6-bit
-  else pos = before - c8 - c6;                               // 4-bit: the first blocks
+  if (rank < c8) pos = c4 + c6 + rank;                       // 8-bit: the last blocks
+  else if (rank < c8 + c6) pos = c4 + (rank - c8);           // 6-bit
+  else pos = rank - c8 - c6;                                 // 4-bit: the first blocks
   perm[pos] = (int32_t)i;
+}
+
+template <class Samples>
+hipError_t go_colsq(const Samples &sm, int64_t n, int64_t K, double *out, bool accumulate,
+                    hipStream_t stream) {
+  const int64_t blocks = (K + kColLanes - 1) / kColLanes;
+  hipLaunchKernelGGL(colsq_kernel<Samples>, dim3((unsigned)blocks, (unsigned)n), dim3(kColLanes), 0,
+                     stream, sm, K, out, accumulate ? 1 : 0);
+  return hipGetLastError();
+}
+
+hipError_t go_add(const double *part, int64_t n, int64_t K, double *s, bool accumulate,
+                  hipStream_t stream) {
+  const int64_t blocks = (K + kCalThreads - 1) / kCalThreads;
+  hipLaunchKernelGGL(add_samples_kernel, dim3((unsigned)blocks), dim3(kCalThreads), 0, stream,
+                     part, n, K, s, accumulate ? 1 : 0);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_calib_colsq(const uint16_t *x, int64_t rows, int64_t ld, int64_t K, double *s,
                               bool accumulate, hipStream_t stream) {
-  const int64_t blocks = (K + kCalThreads - 1) / kCalThreads;
-  hipLaunchKernelGGL(colsq_kernel, dim3((unsigned)blocks), dim3(kCalThreads), 0, stream, x, rows,
-                     ld, K, s, accumulate ? 1 : 0);
-  return hipGetLastError();
+  return go_colsq(SampleBatch{x, 0, rows, ld}, 1, K, s, accumulate, stream);
 }
 
 hipError_t launch_calib_colsq_samples(const uint16_t *x, int64_t n, int64_t rows, int64_t ld,
                                       int64_t sample_stride, int64_t K, double *part, double *s,
                                       bool accumulate, hipStream_t stream) {
-  const int64_t blocks = (K + kCalThreads - 1) / kCalThreads;
-  hipLaunchKernelGGL(colsq_samples_kernel, dim3((unsigned)blocks, (unsigned)n), dim3(kCalThreads),
-                     0, stream, x, rows, ld, sample_stride, K, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(add_samples_kernel, dim3((unsigned)blocks), dim3(kCalThreads), 0, stream,
-                     part, n, K, s, accumulate ? 1 : 0);
-  return hipGetLastError();
+  const hipError_t e = go_colsq(SampleBatch{x, sample_stride, rows, ld}, n, K, part, false, stream);
+  return e != hipSuccess ? e : go_add(part, n, K, s, accumulate, stream);
+}
+
+hipError_t launch_calib_colsq_list(const uint16_t *const *x, const int64_t *rows,
+                                   const int64_t *ld, int64_t n, int64_t K, double *part,
+                                   double *s, bool accumulate, hipStream_t stream) {
+  SampleList l{};
+  for (int64_t i = 0; i < n; ++i) {
+    l.x[i] = x[i];
+    l.rows[i] = rows[i];
+    l.ld[i] = ld[i];
+  }
+  const hipError_t e = go_colsq(l, n, K, part, false, stream);
+  return e != hipSuccess ? e : go_add(part, n, K, s, accumulate, stream);
 }
 
 hipError_t launch_calib_perm(const double *s, int64_t K, int64_t n6, int64_t n8, int32_t *perm,
                              hipStream_t stream) {
-  const int64_t blocks = (K + kCalThreads - 1) / kCalThreads;
+  const int64_t blocks = (K + kRankCols - 1) / kRankCols;
   hipLaunchKernelGGL(rank_perm_kernel, dim3((unsigned)blocks), dim3(kCalThreads), 0, stream, s,
                      K, K / 32 - n6 - n8, n6, n8, perm);
   return hipGetLastError();

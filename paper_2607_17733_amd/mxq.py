@@ -55,6 +55,7 @@ _SIGS = {
     "mxq_calib_colsq": (ctypes.c_int, [_P, _I64, _I64, _I64, _P, ctypes.c_int, _P]),
     "mxq_calib_colsq_samples": (ctypes.c_int, [_P, _I64, _I64, _I64, _I64, _I64, _P, _P,
                                                ctypes.c_int, _P]),
+    "mxq_calib_colsq_list": (ctypes.c_int, [_P, _P, _P, _I64, _I64, _P, _P, ctypes.c_int, _P]),
     "mxq_calib_ratio": (ctypes.c_int, [ctypes.c_int32, _P, _P, ctypes.c_double, _P]),
     "mxq_calib_counts": (ctypes.c_int, [_I64, ctypes.c_double, ctypes.c_double,
                                         ctypes.c_int32, _P, _P, _P]),
@@ -428,12 +429,40 @@ def calib_perm(s, n6: int, n8: int, perm=None):
     return perm
 
 
+CALIB_LIST_MAX = 32
+
+
+def _colsq_list(samples):
+    """Sensitivities of samples that lie on the device together, a launch per
+    CALIB_LIST_MAX samples: one sample's columns fill a fraction of the GPU.
+    None for samples that are not all bf16 [rows, K] of one K and device
+    (they are summed one call each)."""
+    if len(samples) < 2 or not all(isinstance(x, torch.Tensor) and x.dim() == 2
+                                   and x.dtype == torch.bfloat16 and x.stride(1) == 1
+                                   and x.shape[1] == samples[0].shape[1]
+                                   and x.device == samples[0].device for x in samples):
+        return None
+    K, dev = samples[0].shape[1], samples[0].device
+    s = torch.empty(K, dtype=torch.float64, device=dev)
+    work = torch.empty(min(len(samples), CALIB_LIST_MAX) * K, dtype=torch.float64, device=dev)
+    for i in range(0, len(samples), CALIB_LIST_MAX):
+        part = samples[i:i + CALIB_LIST_MAX]
+        n = len(part)
+        _check(lib().mxq_calib_colsq_list((_P * n)(*[x.data_ptr() for x in part]),
+                                          (_I64 * n)(*[x.shape[0] for x in part]),
+                                          (_I64 * n)(*[x.stride(0) for x in part]), n, K,
+                                          _ptr(work), _ptr(s), 1 if i else 0, _stream()),
+               "mxq_calib_colsq_list")
+    return s
+
+
 def calibrate(samples, s_layer: float, R: float, n8_blocks: int = 1):
     """One layer: sensitivities over the samples, the block counts and the
     permutation.  Returns (perm int32 device tensor, widths list)."""
-    s = None
-    for i, x in enumerate(samples):
-        s = calib_colsq(x, s, accumulate=i > 0)
+    s = _colsq_list(samples) if isinstance(samples, (list, tuple)) else None
+    if s is None:
+        for i, x in enumerate(samples):
+            s = calib_colsq(x, s, accumulate=i > 0)
     K = s.numel()
     n4, n6, n8 = calib_counts(K, R, s_layer, n8_blocks)
     perm = calib_perm(s, n6, n8)

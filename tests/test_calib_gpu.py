@@ -98,3 +98,31 @@ def test_colsq_samples_equals_per_sample_calls(n, rows, K):
     s1 = mxq.calib_colsq_samples(x)
     torch.cuda.synchronize()
     assert np.array_equal(s1.cpu().numpy(), calib.column_sensitivity(samples))
+
+
+@pytest.mark.parametrize("rows,K", [((1, 31), 32), ((33, 64), 96), ((95, 96, 97, 128, 5), 544),
+                                    ((40,) * 35, 192)])
+def test_sample_lists_equal_per_sample_calls(rows, K):
+    """Samples calibrated in one launch: row counts on both sides of the
+    kernel's batches of 32 rows, strided rows, more samples than a launch
+    takes; the sums through the permutation they give."""
+    say("calib-list", len(rows), K)
+    samples = [_samples(7 * i + K, 1, r, K, K + 8 * (i % 2))[0] for i, r in enumerate(rows)]
+    xs = [to_dev_bf16(b)[:, :K] for b in samples]
+    s = mxq._colsq_list(xs)
+    ref = calib.column_sensitivity([b[:, :K] for b in samples])
+    assert np.array_equal(s.cpu().numpy(), ref)
+    perm, widths = mxq.calibrate(xs, 0.5, 0.2)
+    n4, n6, n8 = calib.counts(K, 0.2, 0.5)
+    ref_perm, ref_widths = calib.allocate(ref, n6, n8)
+    assert np.array_equal(perm.cpu().numpy(), ref_perm)
+    assert list(widths) == ref_widths.tolist()
+
+
+def test_samples_of_mixed_width_are_summed_one_by_one():
+    say("calib-mixed")
+    a, b = (to_dev_bf16(_samples(3 + w, 1, 40, w)[0]) for w in (128, 64))
+    assert mxq._colsq_list([a, b]) is None
+    perm, _ = mxq.calibrate([a, b], 0.5, 0.2)
+    s = mxq.calib_colsq(b, mxq.calib_colsq(a), accumulate=True)
+    assert torch.equal(perm, mxq.calib_perm(s, *mxq.calib_counts(128, 0.2, 0.5)[1:]))
