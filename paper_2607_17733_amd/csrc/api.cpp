@@ -115,7 +115,14 @@ mxq_status quantize_common(const mxq_fmt *fmt, const uint16_t *src, int64_t rows
     a.out_rows = round_up(rows, mxq::kWCols);
     a.mant = mant;
     a.exp = exp;
-    return launched(mxq::launch_quantize(a, true, (hipStream_t)stream));
+    a.w_super = mxq::w_super_bytes(l_geo(s), full_clamp(fmt));
+    a.w_super_sc = mxq::w_super_scale_bytes(l_geo(s));
+    // rows that fit in LDS share the activations' kernel
+    if (mxq::quantize_act_lds(fmt->K) <= mxq::kMaxLds) {
+      a.weights = 1;
+      return launched(mxq::launch_quantize_act(a, (hipStream_t)stream));
+    }
+    return launched(mxq::launch_quantize(a, (hipStream_t)stream));
   }
   a.canon_rb = canon_rb(s);
   a.canon_erb = exp_rb(fmt);
@@ -128,7 +135,6 @@ mxq_status quantize_common(const mxq_fmt *fmt, const uint16_t *src, int64_t rows
     a.out_rb = canon_rb(s);
     a.out_erb = exp_rb(fmt);
   } else {
-    a.write_image = 1;
     a.out_rows = round_up(rows, mxq::kATileRows);
     a.img = mant;
     a.img_exp = exp;
@@ -136,8 +142,7 @@ mxq_status quantize_common(const mxq_fmt *fmt, const uint16_t *src, int64_t rows
     a.a_tile_sc = mxq::a_tile_scale_bytes(l_geo(s));
   }
   // the activation quantizer stages its rows in LDS: one row must fit
-  if (mxq::quantize_act_lds(fmt->K, mxq::quantize_act_padded_blocks(s.n3, s.n4, s.n6, s.n8),
-                            fmt->perm != nullptr, gain != nullptr) > mxq::kMaxLds)
+  if (mxq::quantize_act_lds(fmt->K, gain != nullptr) > mxq::kMaxLds)
     return MXQ_ERR_UNSUPPORTED;
   return launched(mxq::launch_quantize_act(a, (hipStream_t)stream));
 }

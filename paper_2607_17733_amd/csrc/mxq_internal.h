@@ -29,15 +29,15 @@ struct QuantArgs {
   int64_t canon_erb;       // exponent bytes per row
   int64_t row_used;        // unpadded packed bytes per row
   // activations: which outputs to write
-  int write_rows, write_image;
+  int write_rows;          // packed rows (else the operand image)
   uint8_t *img;            // operand image (16-row tiles)
   uint8_t *img_exp;        // its scale words
   int64_t a_tile, a_tile_sc;  // bytes per 16-row tile of each
-  int stage;               // weights: stage source rows in LDS before the gather
+  int weights;             // the weight layout (the rows are weight columns)
+  int64_t w_super, w_super_sc;  // its bytes per 128-column super-slab
   int vec16;               // 16-byte source loads are aligned
-  int rows_per_wg;         // filled by the launcher
   int lg_rows;             // activations: log2 of the rows per group
-  int perm_table;          // activations: gather through the LDS offset table
+  int silu_table;          // SiLU(gate) from a table in LDS
   // activations: RMS-normalise each row before quantizing (y = g * x / rms)
   int rmsnorm;
   const uint16_t *gain;    // bf16 [K]
@@ -76,11 +76,9 @@ struct UnpackArgs {
 
 constexpr int64_t kMaxLds = 160 * 1024;   // LDS per workgroup on gfx950
 
-hipError_t launch_quantize(const QuantArgs &args, bool weights, hipStream_t s);
+hipError_t launch_quantize(const QuantArgs &args, hipStream_t s);
 hipError_t launch_quantize_act(const QuantArgs &args, hipStream_t s);
-int quantize_act_padded_blocks(int n3, int n4, int n6, int n8);
-int quantize_act_rows(int64_t K, int padded_blocks, bool perm, bool rmsnorm = false);
-int64_t quantize_act_lds(int64_t K, int padded_blocks, bool perm, bool rmsnorm = false);
+int64_t quantize_act_lds(int64_t K, bool rmsnorm = false);   // bytes of a staged row
 // Compute units of the current device (256 if the query fails).
 int device_cu_count();
 hipError_t launch_gemm_prefill(const GemmArgs &args, hipStream_t s);

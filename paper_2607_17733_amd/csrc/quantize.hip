@@ -4,12 +4,12 @@
 // block of the permuted weight row (one output column) gets one shared
 // exponent and one mantissa width, the same quantizer as the activations.
 //
-// Work decomposition: a thread owns 8 consecutive elements of a block (a
-// "quarter"), so the 4 threads of a block are adjacent lanes; the block
-// maximum is a 2-step xor-shuffle reduction of integer |bf16| bit patterns.
-// A workgroup owns one row (K >= 2048) or several whole rows (short K).
-// With a column permutation the workgroup first stages its source rows in
-// LDS with 16-byte coalesced loads and gathers from LDS.
+// This is the kernel of rows too long to be staged in LDS (more than about 80
+// thousand columns); shorter ones take the activation quantizer's kernel.  A
+// workgroup owns one row and gathers it from global memory.  A thread owns 8
+// consecutive elements of a block (a "quarter"), so the 4 threads of a block
+// are adjacent lanes; the block maximum is a 2-step xor-shuffle reduction of
+// integer |bf16| bit patterns.
 //
 // Output: the weight layout of both GEMMs (LGeo in mxq_device.h), one copy
 // at the MXINT size: the folded FP6 codes of 3- and 4-bit blocks, the two
@@ -49,7 +49,6 @@ __device__ inline void quarter_words(const uint32_t *c, int kg, uint32_t *d) {
 }
 
 __global__ __launch_bounds__(kThreads) void quantize_kernel(QuantArgs q) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int t = threadIdx.x;
   const int64_t K = q.K;
   const LGeo lg(q.n3, q.n4, q.n6, q.n8);
@@ -57,39 +56,9 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(QuantArgs q) {
   int npb = 0;                               // padded blocks of a column
   for (int s = 0; s < kSegs; ++s) npb += lg.S[s] * (s < 2 ? 4 : 2);
   const int G = 4 * npb;                     // quarters per column
-  const int R = q.rows_per_wg;
-  const int64_t row0 = (int64_t)blockIdx.x * R;
-  uint16_t *srow = (uint16_t *)smem;         // [R][K] staged source rows
+  const int64_t row = blockIdx.x;            // the weight column
 
-  if (q.stage) {
-    const int64_t total = (int64_t)R * K;
-    if (q.vec16) {
-      for (int64_t v = t; v < total / 8; v += kThreads) {
-        const int lr = (int)(v * 8 / K);
-        const int64_t col = v * 8 - (int64_t)lr * K;
-        const int64_t row = row0 + lr;
-        uint4 d = make_uint4(0, 0, 0, 0);
-        if (row < q.src_rows) d = *(const uint4 *)(q.src + row * q.ld + col);
-        *(uint4 *)(srow + (int64_t)lr * K + col) = d;
-      }
-    } else {
-      for (int64_t v = t; v < total; v += kThreads) {
-        const int lr = (int)(v / K);
-        const int64_t col = v - (int64_t)lr * K;
-        const int64_t row = row0 + lr;
-        srow[v] = row < q.src_rows ? q.src[row * q.ld + col] : (uint16_t)0;
-      }
-    }
-    __syncthreads();
-  }
-
-  for (int64_t f = t; f < (int64_t)R * G; f += kThreads) {
-    const int lr = (int)(f / G);
-    const int gq = (int)(f - (int64_t)lr * G);
-    const int64_t row = row0 + lr;           // the weight column
-    // the last workgroup's rows may pass the padded column count (a block's
-    // four quarters skip together, so the shuffles stay within live lanes)
-    if (row >= q.out_rows) continue;
+  for (int gq = t; gq < G; gq += kThreads) {
     const int pb = gq >> 2, kg = gq & 3;
     // segment, step, position within the step, and the width-map block
     int s = 0, rem = pb;
@@ -117,7 +86,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(QuantArgs q) {
       for (int u = 0; u < 8; ++u) {
         const bool ok = src[u] >= 0 && (int64_t)src[u] < K;
         uint32_t v = 0;
-        if (ok) v = q.stage ? srow[(int64_t)lr * K + src[u]] : q.src[row * q.ld + src[u]];
+        if (ok) v = q.src[row * q.ld + src[u]];
         bits[u] = v;
       }
     } else if (q.vec16) {
@@ -228,25 +197,10 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(QuantArgs q) {
 
 }  // namespace
 
-hipError_t launch_quantize(const QuantArgs &args, bool weights, hipStream_t stream) {
-  if (!weights) return hipErrorInvalidValue;     // activations: launch_quantize_act
-  const LGeo lg(args.n3, args.n4, args.n6, args.n8);
-  int npb = 0;
-  for (int s = 0; s < kSegs; ++s) npb += lg.S[s] * (s < 2 ? 4 : 2);
-  const int G = 4 * npb;
-  QuantArgs a = args;
-  a.rows_per_wg = G >= kThreads ? 1 : kThreads / G;
-  const int64_t grid = (a.out_rows + a.rows_per_wg - 1) / a.rows_per_wg;
-  if (grid <= 0) return hipSuccess;
-  // stage the source rows in LDS for the permutation gather when they fit;
-  // longer rows gather straight from global memory
-  a.stage = (a.perm && (int64_t)a.rows_per_wg * a.K * 2 <= kMaxLds) ? 1 : 0;
-  const int64_t lds = a.stage ? (int64_t)a.rows_per_wg * a.K * 2 : 0;
-  if (lds > kMaxLds) return hipErrorInvalidValue;
-  (void)hipFuncSetAttribute((const void *)quantize_kernel,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
-  hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)grid), dim3(kThreads), (size_t)lds, stream,
-                     a);
+hipError_t launch_quantize(const QuantArgs &args, hipStream_t stream) {
+  if (args.out_rows <= 0) return hipSuccess;
+  hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)args.out_rows), dim3(kThreads), 0, stream,
+                     args);
   return hipGetLastError();
 }
 

@@ -5,18 +5,17 @@
 // + 127 and mantissas of its own width m in {4, 6, 8} (or 3, stored as 2q in
 // the 4-bit layout).
 //
-// Work decomposition.  A workgroup owns R consecutive rows (8 for K = 4096,
-// fewer for longer rows, up to 64 for short ones) and stages them in LDS with
-// 16-byte loads, so the permutation becomes an LDS gather (entries outside
-// [0, K) clamp to the zero padding after the row).  The workgroup first turns
-// the permutation into a table of 16-bit byte offsets in LDS (rows of at most
-// 32767 elements; longer rows read it from global memory per item).  A thread
-// owns one (row, block) item, at most two; its segment selects a code path
-// compiled for that width.  A workgroup has up to 1024 threads and fills a
-// CU.  Lanes run over rows fastest, so the rows of a block write contiguous
-// runs of the 32-row operand tiles (whole 128-byte lines at R = 8), and
-// consecutive workgroups run on one XCD, whose L2 then completes every line
-// of the tile.
+// Work decomposition.  A workgroup owns R consecutive rows (1 to 64, by the
+// number of rows and CUs) and stages them in LDS, so the permutation becomes
+// an LDS gather (entries outside [0, K) take the zero padding after the row).
+// The (row, padded block) items come in chunks of 64, a wave each, that never
+// straddle two segments, so a wave runs the code of one width.  Lanes run
+// over rows fastest, so the rows of a block write contiguous runs of the
+// operand tiles (whole 128-byte lines at R = 8), and consecutive workgroups
+// run on one XCD, whose L2 then completes every line of the tile.  The same
+// kernel packs the weights (a row is a weight column): 14336 x 4096 in 37 us
+// (155 MB), where a workgroup per row with a quarter block per thread took
+// 173.
 //
 // Arithmetic.  The block maximum is taken on the integer |bf16| patterns (two
 // per register); the mantissas are computed in fp32, where every step is
@@ -26,6 +25,7 @@
 // are exact in the target format, so they never round).
 #include "mxq_device.h"
 #include "mxq_internal.h"
+#include <algorithm>
 
 namespace mxq {
 
@@ -140,30 +140,125 @@ __device__ inline ItemGeo item_geo_seg(const LGeo &lg, int rem) {
   g.byte = k & (kGroupSteps - 1);
   return g;
 }
-// First padded block of each segment (P[0] = 0).
-struct SegStarts {
-  int P[kSegs];
-  __device__ explicit SegStarts(const LGeo &lg) {
-    P[0] = 0;
+// The items of a row group in chunks of 64 (a wave each), every chunk inside
+// one segment, so that a wave runs one segment's code: W[s] chunks hold the
+// padded blocks of segment s of the group's 2^lg rows.
+struct Chunks {
+  int W[kSegs], total;
+  __device__ Chunks(const LGeo &lg, int lg_rows) {
+    total = 0;
 #pragma unroll
-    for (int i = 1; i < kSegs; ++i) P[i] = P[i - 1] + lg.S[i - 1] * (i - 1 < 2 ? 4 : 2);
+    for (int s = 0; s < kSegs; ++s) {
+      W[s] = (((lg.S[s] * (s < 2 ? 4 : 2)) << lg_rows) + 63) >> 6;
+      total += W[s];
+    }
   }
 };
-__device__ inline ItemGeo item_geo(const LGeo &lg, const SegStarts &ss, int bp) {
-  if (bp < ss.P[1]) return item_geo_seg<0>(lg, bp);
-  if (bp < ss.P[2]) return item_geo_seg<1>(lg, bp - ss.P[1]);
-  if (bp < ss.P[3]) return item_geo_seg<2>(lg, bp - ss.P[2]);
-  return item_geo_seg<3>(lg, bp - ss.P[3]);
+
+// What a launch writes: the GEMMs' operand image of activations, packed rows,
+// or the weight layout (the row is a weight column).
+enum { kModeImage, kModeRows, kModeWeights };
+// Where the rows come from: as they are, RMS-normalised, SiLU(gate) * up.
+enum { kProdNone, kProdRms, kProdSwiglu };
+
+// Block `pos` of step (segment SEG, padded block rem) of weight column `row`:
+// its codes in the layout both GEMMs read (LGeo in mxq_device.h) and its
+// scale bytes.  v holds the block's mantissas, Eu its exponent.  The FP6
+// codes s|k are the e3m2 codes of q / 16 (linear in k, so the scaled
+// conversion writes them; adding +0 first gives a zero mantissa the sign 0).
+template <int SEG, bool FULL>
+__device__ inline void store_weights(const QuantArgs &q, const LGeo &lg, const ItemGeo &g,
+                                     int64_t row, Blk &v, uint32_t Eu) {
+  constexpr int CB = w_chunk_bytes(SEG, FULL);
+  const int k = g.rem >> (SEG < 2 ? 2 : 1);          // step within the segment
+  const int n = (int)(row & (kWCols - 1)) >> 4, c = (int)row & 15;
+  uint8_t *chunk = q.mant + (row / kWCols) * q.w_super + w_seg_base<SEG, FULL>(lg) +
+                   ((int64_t)k * kWSlabs + n) * CB;
+  uint8_t *scl = q.exp + (row / kWCols) * q.w_super_sc + (int64_t)g.group * 2048 + n;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    v.e[i] += 0.f;
+    v.o[i] += 0.f;
+  }
+  const int l = 16 * g.pos + c;
+  if (SEG <= 1) {
+    const v6u w = to_e3m2(v, 16.f);
+    const uint32_t d[6] = {w[0], w[1], w[2], w[3], w[4], w[5]};
+    uint32_t x[4];
+    if (SEG == 0 && !FULL) {
+      fold3(d, x);
+      *(u2 *)(chunk + 8 * l) = u2{x[0], x[1]};
+      *(uint32_t *)(chunk + 512 + 4 * l) = x[2];
+    } else if (SEG == 1 && FULL) {
+      *(u4 *)(chunk + 16 * l) = u4{d[0], d[1], d[2], d[3]};
+      *(u2 *)(chunk + 1024 + 8 * l) = u2{d[4], d[5]};
+    } else {
+      fold4(d, x);
+      *(u4 *)(chunk + 16 * l) = u4{x[0], x[1], x[2], x[3]};
+    }
+    scl[32 * l + 8 * g.byte] = (uint8_t)Eu;
+  } else if (SEG == 2) {
+    // |q| = 8h + l, both planes with q's sign
+    Blk h, lo;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      h.e[i] = truncf(v.e[i] * 0.125f);
+      h.o[i] = truncf(v.o[i] * 0.125f);
+      lo.e[i] = copysignf(fmaf(h.e[i], -8.f, v.e[i]), v.e[i]);
+      lo.o[i] = copysignf(fmaf(h.o[i], -8.f, v.o[i]), v.o[i]);
+    }
+    const v6u wl = to_e3m2(lo, 16.f), wh = to_e3m2(h, 16.f);
+    const uint32_t dl[6] = {wl[0], wl[1], wl[2], wl[3], wl[4], wl[5]};
+    uint32_t x[4];
+    fold4(dl, x);
+    *(u4 *)(chunk + 16 * l) = u4{x[0], x[1], x[2], x[3]};
+    if (FULL) {
+      const uint32_t dh[6] = {wh[0], wh[1], wh[2], wh[3], wh[4], wh[5]};
+      fold4(dh, x);
+      *(u4 *)(chunk + 512 + 16 * l) = u4{x[0], x[1], x[2], x[3]};
+    } else {
+      // the high plane's magnitudes only: the sign is the low plane's
+      const uint32_t dh[6] = {wh[0] & kF2Q0, wh[1] & kF2Q1, wh[2] & kF2Q2,
+                              wh[3] & kF2Q0, wh[4] & kF2Q1, wh[5] & kF2Q2};
+      fold2(dh, x);
+      *(u2 *)(chunk + 512 + 8 * l) = u2{x[0], x[1]};
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      u4 w;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        uint32_t b = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          b |= w_code8((int)v[16 * j + 4 * d + i], FULL) << (8 * i);
+        w[d] = b;
+      }
+      *(u4 *)(chunk + 32 * l + 16 * j) = w;
+    }
+  }
+  if (SEG >= 2) {
+    scl[32 * (32 * g.pos + c) + 8 * g.byte] = (uint8_t)Eu;
+    scl[32 * (32 * g.pos + 16 + c) + 8 * g.byte] = (uint8_t)Eu;
+  }
+  // the unused scale bytes of a segment's short last group
+  if (g.rem == 0) {
+    const int S = lg.S[SEG], G0 = lg.G0[SEG];
+    for (int kk = S; kk < (S + kGroupSteps - 1) / kGroupSteps * kGroupSteps; ++kk) {
+      uint8_t *z = q.exp + (row / kWCols) * q.w_super_sc +
+                   (int64_t)(G0 + kk / kGroupSteps) * 2048 + 8 * (kk % kGroupSteps) + n;
+      for (int gg = 0; gg < 4; ++gg) z[32 * (16 * gg + c)] = 0;
+    }
+  }
 }
 
-// One (row, padded block) item: gather, quantize, write the canonical
-// packed row and exponent (q.write_rows) and / or the GEMM operand image
-// and its scale words (q.write_image).  sr is the staged row in LDS,
-// followed by zero padding; pt is the permutation as byte offsets into a
-// staged row (two 16-bit offsets per dword), or null for the identity.
-template <bool RNA, int SEG>
+// One (row, padded block) item: gather, quantize, write what MODE names.  sr
+// is the row, in LDS followed by zero padding (or, with the identity
+// permutation, in global memory).
+template <bool RNA, int MODE, int SEG>
 __device__ inline void quantize_item(const QuantArgs &q, const LGeo &lg, const ItemGeo &g,
-                                     const uint32_t *pt, int64_t row, const uint8_t *sr) {
+                                     int64_t row, const uint8_t *sr) {
   constexpr int s = SEG;
   constexpr int m = s == 0 ? 3 : s == 1 ? 4 : s == 2 ? 6 : 8;
   const int rem = g.rem, pos = g.pos, b = g.b;
@@ -182,23 +277,8 @@ __device__ inline void quantize_item(const QuantArgs &q, const LGeo &lg, const I
 #pragma unroll
       for (int k = 0; k < 4; ++k) pr[4 * u + k] = d[k];
     }
-  } else if (pt) {
-    // the block's 32 byte offsets (entries outside [0, K) point at the zero
-    // after the row)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const u4 o = *(const u4 *)(pt + 16 * b + 4 * u);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        v2us x;
-        x.x = *(const uint16_t *)(sr + (o[k] & 0xFFFFu));
-        x.y = *(const uint16_t *)(sr + (o[k] >> 16));
-        pr[4 * u + k] = __builtin_bit_cast(uint32_t, x);
-      }
-    }
   } else {
-    // rows too long for the table: the entries from global memory, clamped
-    // to the zero after the row
+    // entries outside [0, K) take the zero after the row
     const unsigned K = (unsigned)q.K;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
@@ -251,7 +331,8 @@ __device__ inline void quantize_item(const QuantArgs &q, const LGeo &lg, const I
   }
   const uint32_t Eu = pad ? 0u : (uint32_t)E;
 
-  if (q.write_rows && !pad) {
+  if (MODE == kModeRows) {
+    if (pad) return;
     q.exp[row * q.out_erb + b] = (uint8_t)E;
     // the block's offset in the packed row: 12, 16, 24 or 32 bytes per block
     const int64_t aoff = s == 0 ? 12LL * b
@@ -277,8 +358,13 @@ __device__ inline void quantize_item(const QuantArgs &q, const LGeo &lg, const I
       for (int d = 0; d < 4; ++d)
         *(u2 *)(p + 8 * d) = u2{bytes4(v, 8 * d), bytes4(v, 8 * d + 4)};
     }
+    return;
   }
-  if (!q.write_image) return;
+  if (MODE == kModeWeights) {
+    if (q.full_clamp) store_weights<SEG, true>(q, lg, g, row, v, Eu);
+    else store_weights<SEG, false>(q, lg, g, row, v, Eu);
+    return;
+  }
 
   // operand image (16-row tiles) and its scale words
   const int r = (int)(row & (kATileRows - 1));
@@ -354,15 +440,14 @@ __device__ inline void quantize_item(const QuantArgs &q, const LGeo &lg, const I
   }
 }
 
-// quantize_item for the item's segment (a branch that is uniform over a
-// wave except where its items straddle two segments)
-template <bool RNA>
-__device__ inline void quantize_item_any(const QuantArgs &q, const LGeo &lg, const ItemGeo &g,
-                                         const uint32_t *pt, int64_t row, const uint8_t *sr) {
-  if (g.s == 0) quantize_item<RNA, 0>(q, lg, g, pt, row, sr);
-  else if (g.s == 1) quantize_item<RNA, 1>(q, lg, g, pt, row, sr);
-  else if (g.s == 2) quantize_item<RNA, 2>(q, lg, g, pt, row, sr);
-  else quantize_item<RNA, 3>(q, lg, g, pt, row, sr);
+// Item `i` of segment SEG: block i >> lg_rows of row i mod 2^lg_rows.
+template <bool RNA, int MODE, int SEG>
+__device__ inline void quantize_chunk(const QuantArgs &q, const LGeo &lg, int i, int64_t r0,
+                                      const uint8_t *rows, int rowB) {
+  const int rem = i >> q.lg_rows, lr = i & ((1 << q.lg_rows) - 1);
+  const int64_t row = r0 + lr;
+  if (rem >= lg.S[SEG] * (SEG < 2 ? 4 : 2) || row >= q.out_rows) return;
+  quantize_item<RNA, MODE, SEG>(q, lg, item_geo_seg<SEG>(lg, rem), row, rows + lr * rowB);
 }
 
 __device__ inline float bf16f(uint32_t b) { return __uint_as_float(b << 16); }
@@ -405,11 +490,49 @@ __device__ inline uint32_t swiglu1(uint32_t g, uint32_t u) {
   return to_bf16(bf16f(to_bf16(s)) * bf16f(u));
 }
 
+// silu(g) by the hardware exponential and reciprocal, for |g| <= 80: at most
+// kSiluUlp float32 units from swiglu1's (over every bf16 gate).  g * kC is
+// exact (8 + 16 significant bits); the rest of log2(e) enters as the factor
+// 2^(-g c) = 1 - g c ln 2.
+constexpr int kSiluUlp = 3;
+__device__ inline float silu_fast(float g) {
+  constexpr float kC = 47274.f / 32768.f;              // log2(e) to 16 bits
+  constexpr float kR = -4.8885e-6f;                    // -(log2(e) - kC) ln 2
+  float e = __builtin_amdgcn_exp2f(g * -kC);
+  e = fmaf(e, g * kR, e);
+  return g * __builtin_amdgcn_rcpf(1.f + e);
+}
+
+// Eight elements of swiglu1.  Its float32 silu is rounded to bf16, so the
+// fast silu gives the same bits unless a rounding boundary lies within its
+// error: vectors with such an element, or with a gate beyond the fast range
+// (NaN and infinities among them), are evaluated as defined (about 5 % of the
+// waves take that branch for one or more lanes).
 __device__ inline u4 swiglu8(u4 g, u4 u) {
+  float s[8];
   u4 o;
+  uint32_t gm = 0, near = 0xFFFFu;
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    o[j] = swiglu1(g[j] & 0xFFFFu, u[j] & 0xFFFFu) | (swiglu1(g[j] >> 16, u[j] >> 16) << 16);
+  for (int j = 0; j < 4; ++j) {
+    s[2 * j] = silu_fast(__uint_as_float(g[j] << 16));
+    s[2 * j + 1] = silu_fast(__uint_as_float(g[j] & 0xFFFF0000u));
+    gm = max(gm, max((g[j] << 16) & 0x7FFF0000u, g[j] & 0x7FFF0000u));
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      near = min(near, (__float_as_uint(s[2 * j + k]) - (0x8000u - kSiluUlp)) & 0xFFFFu);
+  }
+  if (gm > 0x42A00000u || near <= 2 * kSiluUlp) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      o[j] = swiglu1(g[j] & 0xFFFFu, u[j] & 0xFFFFu) | (swiglu1(g[j] >> 16, u[j] >> 16) << 16);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float a = bf16f(to_bf16(s[2 * j])) * __uint_as_float(u[j] << 16);
+      const float b = bf16f(to_bf16(s[2 * j + 1])) * __uint_as_float(u[j] & 0xFFFF0000u);
+      o[j] = to_bf16(a) | (to_bf16(b) << 16);
+    }
+  }
   return o;
 }
 
@@ -479,157 +602,245 @@ __device__ void rms_normalise(const QuantArgs &q, uint8_t *smem, int R, int rowB
   __syncthreads();
 }
 
-template <bool RNA>
+// bf16(silu(g)) of every gate with 2^-14 <= |g| < 2^7 (21 binades of 128
+// values, positive and negative in turn), as swiglu1 defines it: entry
+// rotl16(g) - kSiluLo.
+constexpr int kSiluLo = 2 * (113 << 7), kSiluN = 2 * (21 << 7);
+
+__device__ inline uint32_t rotl16(uint32_t g) { return ((g << 1) | (g >> 15)) & 0xFFFFu; }
+
+// Eight elements of swiglu1, the silu from the table in LDS.  A vector with a
+// gate outside the table is evaluated as defined.
+__device__ inline u4 swiglu8_table(const uint16_t *tab, u4 g, u4 u) {
+  u4 o;
+  bool in = true;
+  uint32_t s[8];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const v2us x = __builtin_bit_cast(v2us, (uint32_t)g[j]);
+    const v2us i = (v2us)((x << 1) | (x >> 15)) - (unsigned short)kSiluLo;
+    in = in && i.x < kSiluN && i.y < kSiluN;
+    s[2 * j] = tab[min((int)i.x, kSiluN - 1)];
+    s[2 * j + 1] = tab[min((int)i.y, kSiluN - 1)];
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    o[j] = to_bf16(bf16f(s[2 * j]) * __uint_as_float(u[j] << 16)) |
+           (to_bf16(bf16f(s[2 * j + 1]) * __uint_as_float(u[j] & 0xFFFF0000u)) << 16);
+  if (!in) o = swiglu8(g, u);
+  return o;
+}
+
+template <bool RNA, int MODE, int PROD>
 __global__ __launch_bounds__(kMaxThreads) void quantize_act_kernel(QuantArgs q) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int t = threadIdx.x;
   const int nthr = blockDim.x;
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), nwaves = nthr >> 6;
   const int K = (int)q.K;
   const int rowB = 2 * (K + kRowPad);                // staged row stride (bytes)
   const int lgR = q.lg_rows;
   const int R = 1 << lgR;
-  const LGeo lg(q.n3, q.n4, q.n6, q.n8);
-  int nbp = 0;                                       // padded blocks per row
-  for (int s = 0; s < kSegs; ++s) nbp += lg.S[s] * (s < 2 ? 4 : 2);
-  // XCD-aware order: consecutive row groups (whole 32-row operand tiles)
-  // stay on one XCD, so its L2 completes every line of the tile.
-  int64_t w = blockIdx.x;
+  // XCD-aware order: consecutive row groups (whole operand tiles) stay on one
+  // XCD, so its L2 completes every line of the tile.
   const int64_t nwg = gridDim.x;
-  if ((nwg & 7) == 0) w = (w & 7) * (nwg >> 3) + (w >> 3);
-  const int64_t r0 = w << lgR;
+  int64_t w0 = blockIdx.x;
+  if ((nwg & 7) == 0) w0 = (w0 & 7) * (nwg >> 3) + (w0 >> 3);
 
-  const int nit = nbp << lgR;
-  const SegStarts ss(lg);
-
-  // The permutation as byte offsets into a staged row, two per dword, in LDS
-  // after the rows (and the normalisation's sums); an entry outside [0, K)
-  // becomes the offset of the zero after the row.  A thread's first
-  // kPermPre groups of four entries are loaded before the rows, so their
-  // latency overlaps the rows' loads.
-  constexpr int kPermPre = 4;
-  uint32_t *pt = nullptr;
-  int4 pp[kPermPre];
-  auto put_perm = [&](int c, const int4 &e) {
-    const unsigned k = (unsigned)K;
-    const uint32_t o0 = 2u * min((unsigned)e.x, k), o1 = 2u * min((unsigned)e.y, k);
-    const uint32_t o2 = 2u * min((unsigned)e.z, k), o3 = 2u * min((unsigned)e.w, k);
-    *(u2 *)(pt + 2 * c) = u2{o0 | (o1 << 16), o2 | (o3 << 16)};
-  };
-  if (q.perm_table) {
-    const int rms = q.rmsnorm ? R * (8 * (K / kBlock) + 4) : 0;
-    pt = (uint32_t *)(smem + ((R * rowB + rms + 15) & ~15));
-#pragma unroll
-    for (int j = 0; j < kPermPre; ++j) {
-      const int c = t + j * nthr;
-      if (c < K / 4) pp[j] = *(const int4 *)(q.perm + 4 * c);
+  const int rms = PROD == kProdRms ? R * (8 * (K / kBlock) + 4) : 0;
+  uint16_t *silu = nullptr;
+  if (PROD == kProdSwiglu && q.silu_table) {
+    silu = (uint16_t *)(smem + ((R * rowB + rms + 15) & ~15));
+    for (int i = t; i < kSiluN; i += nthr) {
+      const uint32_t e = (uint32_t)(i + kSiluLo);
+      silu[i] = (uint16_t)swiglu1(((e >> 1) | (e << 15)) & 0xFFFFu, 0x3F80u);
     }
+    __syncthreads();
   }
+  for (int lr = t; lr < R; lr += nthr) *(u4 *)(smem + lr * rowB + 2 * K) = u4{0u, 0u, 0u, 0u};
 
-  // Stage the rows.  Each thread issues a batch of loads before it stores
-  // any of them, so the batch costs one memory latency instead of one per
-  // load.
-  constexpr int kBatch = 8;
-  if (q.vec16 && !q.swiglu && K % 512 == 0) {
-    // Rows of whole 1 KB pieces go straight into LDS (direct-to-LDS loads,
-    // one piece per wave instruction), so no thread waits for its data
-    // before the permutation table is written.  Rows past the source's end
-    // read zeros: the buffer resource ends at its last row.
-    const int64_t live = q.src_rows > r0 ? q.src_rows - r0 : 0;
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(q.src + r0 * q.ld), 0, (int)min(live * q.ld * 2, (int64_t)0x7fffffff), 0x00020000);
-    const int per_row = K / 512;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), nwaves = nthr >> 6;
-    for (int pc = wave; pc < R * per_row; pc += nwaves) {
-      const int lr = pc / per_row, j = pc - lr * per_row;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(smem + lr * rowB + j * 1024), 16,
-                                               (t & 63) * 16, (int)(lr * q.ld * 2) + j * 1024, 0, 0);
-    }
-  } else if (q.vec16) {
-    // vector v = lr * vpr + c, advanced by nthr without dividing per load
-    const int vpr = K / 8, nv = R * vpr;
-    const int dq = nthr / vpr, dr = nthr - dq * vpr;
-    int lr0 = t / vpr, c0 = t - lr0 * vpr;
-    const bool swiglu = q.swiglu != 0;
-    for (int v0 = t; v0 < nv; v0 += nthr * kBatch) {
-      u4 d[kBatch];
-      int lrk[kBatch], ck[kBatch];
-      int lr = lr0, c = c0;
-#pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        lrk[k] = lr;
-        ck[k] = c;
-        if (v0 + k * nthr < nv) {
-          if (r0 + lr < q.src_rows) {
-            d[k] = *(const u4 *)(q.src + (r0 + lr) * q.ld + 8 * c);
-            if (swiglu) d[k] = swiglu8(d[k], *(const u4 *)(q.src2 + (r0 + lr) * q.ld + 8 * c));
-          } else {
-            d[k] = u4{0u, 0u, 0u, 0u};
-          }
-        }
-        c += dr;
-        lr += dq;
-        if (c >= vpr) {
-          c -= vpr;
+  // With the silu table a workgroup takes a contiguous range of row groups, so
+  // that its tables serve them all; else one.
+  int64_t g0 = w0, g1 = w0 + 1;
+  if (PROD == kProdSwiglu) {
+    const int64_t groups = (q.out_rows + R - 1) >> lgR;
+    const int64_t per = groups / nwg, extra = groups - per * nwg;
+    g0 = w0 * per + min(w0, extra);
+    g1 = g0 + per + (w0 < extra ? 1 : 0);
+  }
+  for (int64_t grp = g0; grp < g1; ++grp) {
+    const int64_t r0 = grp << lgR;
+    // the geometry is formed per group (an opaque zero): held over the loop
+    // its scalars would spill
+    int z = 0;
+    if (PROD == kProdSwiglu) asm volatile("" : "+s"(z));
+    const LGeo lg(q.n3 + z, q.n4 + z, q.n6 + z, q.n8 + z);
+    const Chunks ch(lg, lgR);
+    // Stage the rows.  Each thread issues a batch of loads before it stores
+    // any of them, so the batch costs one memory latency instead of one per
+    // load.
+    constexpr int kBatch = 8;
+    if (PROD != kProdSwiglu && q.vec16 && K % 512 == 0 && R * q.ld * 2 <= 0x7fffffff) {
+      // Rows of whole 1 KB pieces go straight into LDS (direct-to-LDS loads,
+      // one piece per wave instruction), so no thread waits for its data
+      // before the permutation table is written.  Rows past the source's end
+      // read zeros: the buffer resource ends at its last row.
+      const int64_t live = q.src_rows > r0 ? q.src_rows - r0 : 0;
+      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+          (void *)(q.src + r0 * q.ld), 0, (int)min(live * q.ld * 2, (int64_t)0x7fffffff),
+          0x00020000);
+      const int per_row = K / 512;
+      int lr = wave / per_row, j = wave - lr * per_row;
+      const int dl = nwaves / per_row, dj = nwaves - dl * per_row;
+      while (lr < R) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(smem + lr * rowB + j * 1024),
+                                                 16, lane * 16, (int)(lr * q.ld * 2) + j * 1024, 0,
+                                                 0);
+        lr += dl;
+        j += dj;
+        if (j >= per_row) {
+          j -= per_row;
           ++lr;
         }
       }
-      lr0 = lr;
-      c0 = c;
+    } else if (PROD == kProdSwiglu && q.vec16) {
+      // gate and up vectors: a batch of both in flight, then their products
+      constexpr int kPairs = 4;
+      const int vpr = K / 8, nv = R * vpr;
+      const int dq = nthr / vpr, dr = nthr - dq * vpr;
+      int lr = t / vpr, c = t - lr * vpr;
+      for (int v0 = t; v0 < nv; v0 += nthr * kPairs) {
+        u4 g[kPairs], u[kPairs];
+        int off[kPairs];
 #pragma unroll
-      for (int k = 0; k < kBatch; ++k)
-        if (v0 + k * nthr < nv) *(u4 *)(smem + lrk[k] * rowB + 16 * ck[k]) = d[k];
-    }
-  } else {
-    for (int lr = 0; lr < R; ++lr) {
-      const bool live = r0 + lr < q.src_rows;
-      const uint16_t *src = q.src + (r0 + lr) * q.ld;
-      for (int c = t; c < K; c += nthr) {
-        uint32_t v = live ? src[c] : 0u;
-        if (live && q.swiglu) v = swiglu1(v, q.src2[(r0 + lr) * q.ld + c]);
-        *(uint16_t *)(smem + lr * rowB + 2 * c) = (uint16_t)v;
+        for (int k = 0; k < kPairs; ++k) {
+          off[k] = lr * rowB + 16 * c;
+          g[k] = u[k] = u4{0u, 0u, 0u, 0u};
+          if (v0 + k * nthr < nv && r0 + lr < q.src_rows) {
+            const int64_t src = (r0 + lr) * q.ld + 8 * c;
+            g[k] = *(const u4 *)(q.src + src);
+            u[k] = *(const u4 *)(q.src2 + src);
+          }
+          c += dr;
+          lr += dq;
+          if (c >= vpr) {
+            c -= vpr;
+            ++lr;
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k)
+          if (v0 + k * nthr < nv)
+            *(u4 *)(smem + off[k]) = silu ? swiglu8_table(silu, g[k], u[k]) : swiglu8(g[k], u[k]);
+      }
+    } else if (q.vec16) {
+      // vector v = lr * vpr + c, advanced by nthr without dividing per load
+      const int vpr = K / 8, nv = R * vpr;
+      const int dq = nthr / vpr, dr = nthr - dq * vpr;
+      int lr0 = t / vpr, c0 = t - lr0 * vpr;
+      for (int v0 = t; v0 < nv; v0 += nthr * kBatch) {
+        u4 d[kBatch];
+        int lrk[kBatch], ck[kBatch];
+        int lr = lr0, c = c0;
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+          lrk[k] = lr;
+          ck[k] = c;
+          if (v0 + k * nthr < nv) {
+            if (r0 + lr < q.src_rows)
+              d[k] = *(const u4 *)(q.src + (r0 + lr) * q.ld + 8 * c);
+            else
+              d[k] = u4{0u, 0u, 0u, 0u};
+          }
+          c += dr;
+          lr += dq;
+          if (c >= vpr) {
+            c -= vpr;
+            ++lr;
+          }
+        }
+        lr0 = lr;
+        c0 = c;
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k)
+          if (v0 + k * nthr < nv) *(u4 *)(smem + lrk[k] * rowB + 16 * ck[k]) = d[k];
+      }
+    } else {
+      for (int lr = 0; lr < R; ++lr) {
+        const bool live = r0 + lr < q.src_rows;
+        const uint16_t *src = q.src + (r0 + lr) * q.ld;
+        for (int c = t; c < K; c += nthr) {
+          uint32_t v = live ? src[c] : 0u;
+          if (PROD == kProdSwiglu && live) v = swiglu1(v, q.src2[(r0 + lr) * q.ld + c]);
+          *(uint16_t *)(smem + lr * rowB + 2 * c) = (uint16_t)v;
+        }
       }
     }
-  }
-  if (pt) {
-#pragma unroll
-    for (int j = 0; j < kPermPre; ++j) {
-      const int c = t + j * nthr;
-      if (c < K / 4) put_perm(c, pp[j]);
-    }
-    for (int c = t + kPermPre * nthr; c < K / 4; c += nthr)
-      put_perm(c, *(const int4 *)(q.perm + 4 * c));
-  }
-  if (t < R) *(u4 *)(smem + t * rowB + 2 * K) = u4{0u, 0u, 0u, 0u};
-  // the direct-to-LDS loads are complete before the workgroup meets
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (q.rmsnorm) rms_normalise(q, smem, R, rowB, t, nthr, r0);
+    // the direct-to-LDS loads are complete before the workgroup meets
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (PROD == kProdRms) rms_normalise(q, smem, R, rowB, t, nthr, r0);
 
-  for (int it = t; it < nit; it += nthr) {
-    const int lr = it & (R - 1);
-    const int64_t row = r0 + lr;
-    if (row < q.out_rows)
-      quantize_item_any<RNA>(q, lg, item_geo(lg, ss, it >> lgR), pt, row, smem + lr * rowB);
-  }
-  // zero the padding of the packed and exponent rows
-  if (q.write_rows && t < R) {
-    const int64_t row = r0 + t;
-    if (row < q.src_rows) {
-      for (int64_t z = q.row_used; z < q.canon_rb; ++z) q.mant[row * q.out_rb + z] = 0;
-      for (int64_t z = q.n4 + q.n6 + q.n8; z < q.canon_erb; ++z)
-        q.exp[row * q.out_erb + z] = 0;
+    // the widest segments first: their items take longest
+    for (int wc = wave; wc < ch.total; wc += nwaves) {
+      int x = wc;
+      if (x < ch.W[3])
+        quantize_chunk<RNA, MODE, 3>(q, lg, 64 * x + lane, r0, smem, rowB);
+      else if ((x -= ch.W[3]) < ch.W[2])
+        quantize_chunk<RNA, MODE, 2>(q, lg, 64 * x + lane, r0, smem, rowB);
+      else if ((x -= ch.W[2]) < ch.W[1])
+        quantize_chunk<RNA, MODE, 1>(q, lg, 64 * x + lane, r0, smem, rowB);
+      else
+        quantize_chunk<RNA, MODE, 0>(q, lg, 64 * (x - ch.W[1]) + lane, r0, smem, rowB);
     }
+    // zero the padding of the packed and exponent rows
+    if (MODE == kModeRows)
+      for (int lr = t; lr < R; lr += nthr) {
+        const int64_t row = r0 + lr;
+        if (row < q.src_rows) {
+          for (int64_t z = q.row_used; z < q.canon_rb; ++z) q.mant[row * q.out_rb + z] = 0;
+          for (int64_t z = q.n4 + q.n6 + q.n8; z < q.canon_erb; ++z)
+            q.exp[row * q.out_erb + z] = 0;
+        }
+      }
+    if (PROD != kProdSwiglu) break;
+    if (grp + 1 < g1) __syncthreads();               // the rows are consumed
+  }
+}
+
+// Packed rows of the identity permutation (the KV cache): a block's 64 bytes
+// are contiguous, so a lane reads its block itself and nothing is staged.
+// Lanes run over the blocks of a row, then over rows: the reads and the packed
+// rows are contiguous over a wave.
+constexpr int kRowsThreads = 256;
+
+template <bool RNA>
+__global__ __launch_bounds__(kRowsThreads) void quantize_rows_kernel(QuantArgs q) {
+  const LGeo lg(q.n3, q.n4, q.n6, q.n8);
+  const int nb = (int)(q.K / kBlock);
+  const int64_t it = (int64_t)blockIdx.x * kRowsThreads + threadIdx.x;
+  const int64_t row = it / nb;
+  const int b = (int)(it - row * nb);
+  if (row >= q.src_rows) return;
+  const uint8_t *sr = (const uint8_t *)(q.src + row * q.ld);
+  if (b < lg.b0[1])
+    quantize_item<RNA, kModeRows, 0>(q, lg, item_geo_seg<0>(lg, b), row, sr);
+  else if (b < lg.b0[2])
+    quantize_item<RNA, kModeRows, 1>(q, lg, item_geo_seg<1>(lg, b - lg.b0[1]), row, sr);
+  else if (b < lg.b0[3])
+    quantize_item<RNA, kModeRows, 2>(q, lg, item_geo_seg<2>(lg, b - lg.b0[2]), row, sr);
+  else
+    quantize_item<RNA, kModeRows, 3>(q, lg, item_geo_seg<3>(lg, b - lg.b0[3]), row, sr);
+  if (b == 0) {
+    for (int64_t z = q.row_used; z < q.canon_rb; z += 4)
+      *(uint32_t *)(q.mant + row * q.out_rb + z) = 0;
+    int64_t z = nb;
+    for (; z & 3; ++z) q.exp[row * q.out_erb + z] = 0;
+    for (; z < q.canon_erb; z += 4) *(uint32_t *)(q.exp + row * q.out_erb + z) = 0;
   }
 }
 
 }  // namespace
-
-int quantize_act_padded_blocks(int n3, int n4, int n6, int n8) {
-  const LGeo lg(n3, n4, n6, n8);
-  int nbp = 0;
-  for (int s = 0; s < kSegs; ++s) nbp += lg.S[s] * (s < 2 ? 4 : 2);
-  return nbp;
-}
 
 // Bytes per staged row: the row and its zero padding, plus with RMS
 // normalisation its block sums and its 1/rms.
@@ -637,63 +848,77 @@ static int64_t row_lds(int64_t K, bool rmsnorm) {
   return 2 * (K + kRowPad) + (rmsnorm ? 8 * (K / kBlock) + 4 : 0);
 }
 
-// The permutation's byte-offset table (16-bit offsets, so rows of at most
-// 32767 elements), with 16 bytes of alignment slack.
-static int64_t perm_table_lds(int64_t K) { return 2 * K + 16; }
-
-// Rows per workgroup: the largest power of two (at most 64) whose staged
-// rows fit the LDS budget with at most two items per thread, halved while
-// the rows and the permutation table exceed the LDS.  More rows per
-// workgroup make longer contiguous runs in the operand tiles.
-int quantize_act_rows(int64_t K, int nbp, bool perm, bool rmsnorm) {
-  const int64_t per = row_lds(K, rmsnorm);
-  int r = 1;
-  while (r < 64 && 2 * r * per <= kLdsBudget && (int64_t)nbp * 2 * r <= 2 * kMaxThreads)
-    r *= 2;
-  if (perm && K <= kPermTableMaxK)
-    while (r > 1 && r * per + perm_table_lds(K) > kMaxLds) r >>= 1;
-  return r;
+// Row groups: R rows (a power of two) and T threads per workgroup.  While one
+// workgroup per CU covers the rows, R is the least that does (more workgroups
+// of fewer rows leave each a shorter chain) and a wave takes one chunk; beyond
+// that two workgroups share a CU, so that one stages rows while the other
+// computes.  Measured, us: M = 1, K = 4096: R = 1 4.3, R = 8 6.5; M = 333: R =
+// 1 / 2 / 4 / 8 5.2 / 4.8 / 5.6 / 6.8; M = 4096: 1024 threads and one
+// workgroup per CU 17.6, two of 512 13.1.
+struct RowGroups {
+  int lg, threads, per_cu;
+};
+static RowGroups row_groups(const QuantArgs &a, int cus) {
+  const int64_t row = row_lds(a.K, a.rmsnorm != 0), extra = a.swiglu ? 2 * kSiluN : 0;
+  auto fits = [&](int lg, int n) { return n * ((row << lg) + 16 + extra) <= kMaxLds; };
+  const LGeo g(a.n3, a.n4, a.n6, a.n8);
+  auto waves = [&](int lg) {
+    int w = 0;
+    for (int s = 0; s < kSegs; ++s) w += (((g.S[s] * (s < 2 ? 4 : 2)) << lg) + 63) / 64;
+    return w;
+  };
+  constexpr int kMaxWaves = kMaxThreads / 64;
+  auto one = [&](int lg) { return RowGroups{lg, 64 * std::min(waves(lg), kMaxWaves), 1}; };
+  for (int lg = 0; lg <= 6 && fits(lg, 1) && waves(lg) <= 2 * kMaxWaves; ++lg)
+    if (((a.out_rows - 1) >> lg) + 1 <= cus) return one(lg);
+  int lg = 0;
+  while (lg < 6 && fits(lg + 1, 2) && waves(lg + 1) <= kMaxWaves + 2) ++lg;
+  if (!fits(lg, 2)) return one(0);
+  // SiLU * up of long rows: its tables and arithmetic outweigh the overlap
+  // (K = 14336, M = 4096: 4 rows and 1024 threads, one per CU, 76 us, 2 rows
+  // and 512 threads, two per CU, 81 us)
+  if (a.swiglu && lg <= 1 && fits(lg + 1, 1)) return RowGroups{lg + 1, kMaxThreads, 1};
+  return RowGroups{lg, 64 * std::min(waves(lg), kMaxWaves / 2), 2};
 }
 
-// Whether the permutation is gathered through the LDS table.
-static bool quantize_act_table(int64_t K, int nbp, bool perm, bool rmsnorm) {
-  return perm && K <= kPermTableMaxK &&
-         quantize_act_rows(K, nbp, perm, rmsnorm) * row_lds(K, rmsnorm) + perm_table_lds(K) <=
-             kMaxLds;
+template <int MODE, int PROD>
+static hipError_t go_quantize(const QuantArgs &a, int64_t grid, int threads, int64_t lds,
+                              hipStream_t stream) {
+  const auto fn = a.ties_away ? quantize_act_kernel<true, MODE, PROD>
+                              : quantize_act_kernel<false, MODE, PROD>;
+  (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)kMaxLds);
+  hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(threads), (size_t)lds, stream, a);
+  return hipGetLastError();
 }
 
-int64_t quantize_act_lds(int64_t K, int nbp, bool perm, bool rmsnorm) {
-  return (int64_t)quantize_act_rows(K, nbp, perm, rmsnorm) * row_lds(K, rmsnorm) +
-         (quantize_act_table(K, nbp, perm, rmsnorm) ? perm_table_lds(K) : 0);
-}
+int64_t quantize_act_lds(int64_t K, bool rmsnorm) { return row_lds(K, rmsnorm); }
 
 hipError_t launch_quantize_act(const QuantArgs &args, hipStream_t stream) {
   QuantArgs a = args;
-  const bool perm = a.perm != nullptr;
-  const int nbp = quantize_act_padded_blocks(a.n3, a.n4, a.n6, a.n8);
-  const int R = quantize_act_rows(a.K, nbp, perm, a.rmsnorm != 0);
-  int lg = 0;
-  while ((1 << lg) < R) ++lg;
-  a.lg_rows = lg;
-  a.rows_per_wg = R;
-  a.stage = 0;
-  a.perm_table = quantize_act_table(a.K, nbp, perm, a.rmsnorm != 0) ? 1 : 0;
-  const int64_t grid = (a.out_rows + R - 1) / R;
-  if (grid <= 0) return hipSuccess;
-  const int64_t lds = quantize_act_lds(a.K, nbp, perm, a.rmsnorm != 0);
+  if (a.out_rows <= 0) return hipSuccess;
+  if (a.write_rows && !a.perm && a.vec16) {
+    const int64_t wg = (a.src_rows * (a.K / kBlock) + kRowsThreads - 1) / kRowsThreads;
+    hipLaunchKernelGGL(a.ties_away ? quantize_rows_kernel<true> : quantize_rows_kernel<false>,
+                       dim3((unsigned)wg), dim3(kRowsThreads), 0, stream, a);
+    return hipGetLastError();
+  }
+  const int cus = device_cu_count();
+  const RowGroups rg = row_groups(a, cus);
+  a.lg_rows = rg.lg;
+  const int64_t groups = ((a.out_rows - 1) >> rg.lg) + 1;
+  // the silu table pays from six times its own size in elements
+  const int64_t grid = a.swiglu ? std::min<int64_t>(groups, (int64_t)rg.per_cu * cus) : groups;
+  int64_t lds = ((row_lds(a.K, a.rmsnorm != 0) << rg.lg) + 15) & ~15;
+  a.silu_table = a.swiglu && a.vec16 && ((groups / grid * a.K) << rg.lg) >= 6 * kSiluN &&
+                 lds + 2 * kSiluN <= kMaxLds;
+  if (a.silu_table) lds += 2 * kSiluN;
   if (lds > kMaxLds) return hipErrorInvalidValue;
-  const int64_t items = (int64_t)nbp * R;
-  const int threads = (int)(items >= kMaxThreads ? kMaxThreads : (items + 63) / 64 * 64);
-  const void *fn = a.ties_away ? (const void *)quantize_act_kernel<true>
-                               : (const void *)quantize_act_kernel<false>;
-  (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
-  if (a.ties_away)
-    hipLaunchKernelGGL(quantize_act_kernel<true>, dim3((unsigned)grid), dim3(threads),
-                       (size_t)lds, stream, a);
-  else
-    hipLaunchKernelGGL(quantize_act_kernel<false>, dim3((unsigned)grid), dim3(threads),
-                       (size_t)lds, stream, a);
-  return hipGetLastError();
+  if (a.weights) return go_quantize<kModeWeights, kProdNone>(a, grid, rg.threads, lds, stream);
+  if (a.write_rows) return go_quantize<kModeRows, kProdNone>(a, grid, rg.threads, lds, stream);
+  if (a.rmsnorm) return go_quantize<kModeImage, kProdRms>(a, grid, rg.threads, lds, stream);
+  if (a.swiglu) return go_quantize<kModeImage, kProdSwiglu>(a, grid, rg.threads, lds, stream);
+  return go_quantize<kModeImage, kProdNone>(a, grid, rg.threads, lds, stream);
 }
 
 }  // namespace mxq

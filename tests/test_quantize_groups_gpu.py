@@ -1,0 +1,94 @@
+"""The quantizer's launch choices against the oracle: the rows a workgroup
+takes (one workgroup per CU, then two sharing a CU), packed rows read straight
+from global memory, the silu table, and weight rows on both sides of the
+staging limit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import fused
+from paper_2607_17733_amd import mxq
+from paper_2607_17733_amd import workloads as W
+from operand_decode import decode_act
+from parity_util import check_pack_w, fmt_for, say, to_dev_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+# 256 CUs: 256 rows and one more, the last single round of 64-row groups and
+# the first of two workgroups per CU, ragged and 1 KB-piece row lengths, long
+# rows whose groups hold one or two rows.
+@pytest.mark.parametrize("M,K,counts,perm,round_", [
+    (256, 96, (1, 1, 1), "random", "rne"), (257, 96, (1, 1, 1), "random", "rna"),
+    (1027, 512, (12, 2, 2), "scales", "rne"), (16384, 64, (1, 0, 1), "random", "rne"),
+    (16401, 64, (1, 1, 0), "identity", "rna"), (2100, 1056, (25, 4, 4), "random", "rne"),
+    (530, 14336, (314, 67, 67), "scales", "rne"), (259, 40960, (1200, 50, 30), "random", "rne"),
+])
+def test_row_groups(M, K, counts, perm, round_):
+    say("row-groups", M, K, counts, perm, round_)
+    case = W.random_case(M + K, M, K, 16, counts, perm=perm)
+    fmt = fmt_for(case, round_)
+    a = to_dev_bf16(case.a_bits)
+    am, ae = mxq.quantize_act(a, fmt)
+    rows, exps = mxq.quantize_rows(a, fmt)
+    torch.cuda.synchronize()
+    qa, ea = oracle.quantize(case.a_bits, perm=case.perm, widths=case.widths,
+                             round_mode=1 if round_ == "rna" else 0)
+    assert np.array_equal(rows.cpu().numpy(), oracle.pack_act(qa, case.widths))
+    assert np.array_equal(exps.cpu().numpy()[:, :K // 32], ea)
+    q, E, pad_ok = decode_act(am.cpu().numpy(), ae.cpu().numpy(), case.widths, M)
+    assert np.array_equal(q, qa) and np.array_equal(E, ea) and pad_ok
+
+
+@pytest.mark.parametrize("M,widths,pad", [(1, "4444", 0), (17, "4468", 0), (63, "3346", 8),
+                                          (65, "8888", 1), (1000, "46666", 24), (33, "3", 5)])
+def test_identity_rows_from_global_memory(M, widths, pad):
+    """Packed rows of the identity permutation; a row stride that is no
+    multiple of 16 bytes takes the staged path."""
+    say("identity-rows", M, widths, pad)
+    widths = [int(w) for w in widths]
+    K = 32 * len(widths)
+    g = np.random.Generator(np.random.PCG64(M))
+    bits = fused.f32_to_bf16((g.normal(size=(M, K + pad)) * 3).astype(np.float32))
+    rows, exps = mxq.quantize_rows(to_dev_bf16(bits)[:, :K], mxq.Format(K, widths))
+    qa, ea = oracle.quantize(np.ascontiguousarray(bits[:, :K]), widths=widths)
+    assert np.array_equal(rows.cpu().numpy(), oracle.pack_act(qa, widths))
+    e = exps.cpu().numpy()
+    assert np.array_equal(e[:, :K // 32], ea) and not e[:, K // 32:].any()
+
+
+@pytest.mark.parametrize("u", [1.0, 1.0078125, -1.9921875])
+def test_every_gate(u):
+    """All 65536 gates: workgroups of few rows evaluate silu with a check of
+    the rounding boundary, workgroups of many read it from their table; both
+    give the definition's bits (8-bit blocks hold all but the last bit of a
+    product; the factors move the boundary)."""
+    say("every-gate", u)
+    K = 4096
+    g = np.random.Generator(np.random.PCG64(5))
+    # gates of one binade share a block, so that no block's largest hides the rest
+    bits = np.arange(65536, dtype=np.uint16).reshape(-1, 32)
+    gate = g.permutation(bits).reshape(16, K)
+    up = np.full((16, K), fused.f32_to_bf16(np.array([u], np.float32))[0], np.uint16)
+    fmt = mxq.Format(K, [8] * (K // 32))
+    am, ae = mxq.quantize_act_swiglu(to_dev_bf16(gate), to_dev_bf16(up), fmt)
+    qa, ea = oracle.quantize(fused.swiglu_bf16(gate, up), widths=fmt.widths)
+    q, E, pad_ok = decode_act(am.cpu().numpy(), ae.cpu().numpy(), fmt.widths, 16)
+    assert np.array_equal(q, qa) and np.array_equal(E, ea) and pad_ok
+    bm, be = mxq.quantize_act_swiglu(to_dev_bf16(np.tile(gate, (128, 1))),
+                                     to_dev_bf16(np.tile(up, (128, 1))), fmt)
+    assert torch.equal(bm.view(128, -1), am.expand(128, -1))
+    assert torch.equal(be.view(128, -1), ae.expand(128, -1))
+
+
+@pytest.mark.parametrize("K,clamp", [(81888, "sym"), (81920, "sym"), (81920, "full")])
+def test_weight_rows_at_the_staging_limit(K, clamp):
+    say("pack-limit", K, clamp)
+    nb = K // 32
+    case = W.random_case(K, 1, K, 5, (nb - 700, 400, 300), perm="random")
+    fmt = fmt_for(case, "rne", clamp)
+    wm, we = mxq.pack_weights(to_dev_bf16(case.w_bits), fmt)
+    qw, ew = oracle.quantize(case.w_bits, perm=case.perm, widths=case.widths,
+                             clamp_mode=1 if clamp == "full" else 0)
+    check_pack_w(case, {"w_mant": wm, "w_exp": we}, qw, ew, fmt)
