@@ -59,8 +59,8 @@ extern "C" {
 
 #define MXQ_ABI_VERSION 12
 #define MXQ_BLOCK 32
-/* mxq_gemm uses the weight-streaming decode kernel for M <= this (up to
- * four 16-row activation tiles per weight read). */
+/* mxq_gemm uses the weight-streaming decode kernel up to this M (up to four
+ * 16-row activation tiles per weight read) where no other is faster. */
 #define MXQ_DECODE_MAX_M 64
 
 typedef enum {
@@ -300,9 +300,10 @@ mxq_status mxq_pack_weights(const mxq_fmt *fmt, const uint16_t *w, int64_t N,
  *   w_mant/w_exp  DEVICE, from mxq_pack_weights with the same fmt and N.
  *   y             DEVICE float [M][ldy], ldy >= N; every y[i][j] with i < M,
  *                 j < N is written, nothing else.
- * M <= MXQ_DECODE_MAX_M runs the weight-streaming decode kernel (each
- * weight step read once for all ceil(M / 16) activation tiles), larger M
- * the tiled prefill kernel; both read the same buffers.  The weights' high
+ * Small M (at most MXQ_DECODE_MAX_M) runs the weight-streaming decode kernel
+ * (each weight step read once for all ceil(M / 16) activation tiles), large
+ * M x N the tiled prefill kernel, what lies between a kernel that splits K
+ * over the waves of a workgroup; all read the same buffers.  The weights' high
  * digit planes take the scale E + 3 (6-bit) or E + 4 (8-bit), which the
  * E8M0 format holds up to 254: a 6-bit weight block with E >= 252 or an
  * 8-bit one with E >= 251 (|w| >= 2^124) makes the outputs it touches NaN.

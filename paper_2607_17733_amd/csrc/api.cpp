@@ -302,8 +302,9 @@ mxq_status mxq_gemm(const mxq_fmt *fmt, int64_t M, int64_t N, const uint8_t *a_m
   g.y = y;
   g.ldy = ldy;
   hipStream_t s = (hipStream_t)stream;
-  return launched(M <= MXQ_DECODE_MAX_M ? mxq::launch_gemm_decode(g, s)
-                                        : mxq::launch_gemm_prefill(g, s));
+  return launched(M <= MXQ_DECODE_MAX_M && !mxq::gemm_takes_split(g)
+                      ? mxq::launch_gemm_decode(g, s)
+                      : mxq::launch_gemm_prefill(g, s));
 }
 
 mxq_status mxq_gemm_partials(const mxq_fmt *fmt, int64_t M, int64_t N,

@@ -597,7 +597,351 @@ void gemm_prefill_kernel(GemmArgs g, int mtiles, int ntiles, int gm, int gn) {
       }
 }
 
+// Grids too small for the kernel above (a prompt chunk of a few hundred rows, or
+// few columns) leave it one short round of workgroups that walk all of K: there
+// a workgroup owns 32 TM x 128 outputs and its KG waves split K, each taking a
+// contiguous share of the steps (whole scale groups, shares of equal cost), and
+// their sums meet in LDS in wave order.  No operand is shared between waves, so
+// there is no staging and no barrier in the loop: a wave loads its weight bytes
+// and activations straight into registers, a step ahead, each weight slot
+// refilled as soon as its operand is restored.  The latency of a step and, over
+// many tiles, the L2 reads of the weights (once per 32 TM rows) bound it.
+template <bool FULL, int KG, int TM, bool ONCE>
+__global__ __launch_bounds__(64 * KG) __attribute__((amdgpu_waves_per_eu(3 - TM, 3 - TM)))
+void gemm_split_kernel(GemmArgs g, int mtiles, int ntiles, int nx) {
+  constexpr int kAux = ONCE ? 2 : 0;              // non-temporal weight loads
+  __shared__ v4f red[KG][16 * TM][64];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l32 = lane & 31, lh = lane >> 5, l16 = lane & 15, hx = l32 >> 4;
+  // XCD x owns the column tiles nt with nt / nx == x (nx > 0), all row tiles
+  // of each, so that its L2 holds their weights; else in order.
+  int mt, nt;
+  {
+    const int pid = blockIdx.x;
+    if (nx > 0) {
+      const int loc = pid >> 3;
+      nt = (pid & 7) * nx + loc / mtiles;
+      mt = loc % mtiles;
+    } else {
+      nt = pid / mtiles;
+      mt = pid - nt * mtiles;
+    }
+  }
+  const int64_t row0 = (int64_t)mt * 32 * TM, col0 = (int64_t)nt * BN;
+  const LGeo lg(g.n3, g.n4, g.n6, g.n8);
+
+  const int64_t last = (g.M - 1) / kATileRows, ta = row0 / kATileRows;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(g.a_mant + ta * g.a_tile), 0,
+      (int)min((last + 1 - ta) * g.a_tile, (int64_t)0x7fffffff), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(g.a_exp + ta * g.a_tile_sc), 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(g.w_mant + (int64_t)nt * g.w_super), 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rws = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(g.w_exp + (int64_t)nt * g.w_super_sc), 0, 0x7fffffff, 0x00020000);
+  const int lk0 = 16 * lh + l16, lk1 = lk0 + 32;
+  int vt[TM];                                 // the lane's image tile of row tile tm
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm) vt[tm] = (int)min((int64_t)(2 * tm + hx), last - ta);
+
+  // This wave's steps [b, e): equal shares of the steps' cost (a step of 3- or
+  // 4-bit blocks 2, of 6-bit blocks 3, of 8-bit blocks 4: measured 0.9, 1.4 and
+  // 1.8 us), cut at scale groups.
+  auto cut = [&](int k) {
+    constexpr int cost[kSegs] = {2, 2, 3, 4};
+    int total = 0;
+#pragma unroll
+    for (int s = 0; s < kSegs; ++s) total += cost[s] * lg.S[s];
+    int c = (int)((int64_t)total * k / KG), at = lg.nsteps;
+    bool found = false;
+#pragma unroll
+    for (int s = 0; s < kSegs; ++s) {
+      if (!found && c < cost[s] * lg.S[s]) {
+        at = lg.st0[s] + min((c / cost[s] + 2) & ~3, lg.S[s]);
+        found = true;
+      }
+      c -= cost[s] * lg.S[s];
+    }
+    return at;
+  };
+  const int kb = cut(wave), ke = cut(wave + 1);
+
+  v16f acc[TM][4];
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int n = 0; n < 4; ++n) acc[tm][n] = v16f{};
+
+  auto run = [&](auto seg) __attribute__((always_inline)) {
+    constexpr int SEG = decltype(seg)::v;
+    constexpr int CB = w_chunk_bytes(SEG, FULL);
+    constexpr bool kQ = (SEG == 0 && !FULL) || (SEG == 1 && FULL) || (SEG == 2 && !FULL);
+    const int sb = max(kb, lg.st0[SEG]), se = min(ke, lg.st0[SEG] + lg.S[SEG]);
+    if (sb >= se) return;
+    const int abase = (int)a_seg_base<SEG>(lg), wbase = (int)w_seg_base<SEG, FULL>(lg);
+    struct WRaw {
+      u4 p, h;
+      u2 q;
+      uint32_t z;
+    };
+    struct Scales {
+      uint32_t a[TM][2];
+      u4 w[2][2];
+    };
+    WRaw w[8];
+    v8i xa[2][TM][2];
+    Scales sc[2];
+    auto load_w = [&](int st, int p) __attribute__((always_inline)) {
+      const int tn = p >> 1, c = p & 1, lk = c ? lk1 : lk0, jc = 16 * c + l16;
+      const int so = wbase + (min(st, se - 1) - lg.st0[SEG]) * kWSlabs * CB + 2 * tn * CB;
+      WRaw &r = w[p];
+      auto b128 = [&](int o) {
+        return __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(rw, hx * CB + o, so, kAux));
+      };
+      auto b64 = [&](int o) {
+        return __builtin_bit_cast(u2, __builtin_amdgcn_raw_buffer_load_b64(rw, hx * CB + o, so, kAux));
+      };
+      if constexpr (SEG == 0 && !FULL) {
+        r.q = b64(8 * lk);
+        r.z = __builtin_amdgcn_raw_buffer_load_b32(rw, hx * CB + 512 + 4 * lk, so, kAux);
+      } else if constexpr (SEG <= 1) {
+        r.p = b128(16 * lk);
+        if constexpr (kQ) r.q = b64(1024 + 8 * lk);
+      } else if constexpr (SEG == 2) {
+        r.p = b128(16 * jc);
+        if constexpr (FULL) r.h = b128(512 + 16 * jc);
+        else r.q = b64(512 + 8 * jc);
+      } else {
+        r.p = b128(32 * jc + 16 * lh);
+      }
+    };
+    auto load_a = [&](v8i (&x)[TM][2], int st) __attribute__((always_inline)) {
+      const int so = abase + (min(st, se - 1) - lg.st0[SEG]) * kLanes * a_lane_bytes(SEG);
+#pragma unroll
+      for (int tc = 0; tc < 2 * TM; ++tc) {
+        const int tm = tc >> 1, c = tc & 1, vb = vt[tm] * (int)g.a_tile;
+        const int lk = c ? lk1 : lk0;
+        const int olo = SEG == 3 ? 32 * lk0 + 16 * c : 24 * lk;
+        const u4 lo = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(ra, vb + olo, so, 0));
+        u4 hi;
+        if constexpr (SEG == 3) {
+          hi = __builtin_bit_cast(
+              u4, __builtin_amdgcn_raw_buffer_load_b128(ra, vb + 32 * lk1 + 16 * c, so, 0));
+        } else {
+          const u2 h2 = __builtin_bit_cast(
+              u2, __builtin_amdgcn_raw_buffer_load_b64(ra, vb + 24 * lk + 16, so, 0));
+          hi = __builtin_shufflevector(h2, h2, 0, 1, -1, -1);
+        }
+        x[tm][c] = (v8i)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+    };
+    auto load_s = [&](Scales &s, int st) __attribute__((always_inline)) {
+      const int grp = lg.G0[SEG] + (min(st, se - 1) - lg.st0[SEG]) / kGroupSteps;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int lk = c ? lk1 : lk0;
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+          s.a[tm][c] = __builtin_amdgcn_raw_buffer_load_b32(rs, vt[tm] * (int)g.a_tile_sc + 4 * lk,
+                                                            grp * 256, 0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          s.w[c][h] = __builtin_bit_cast(
+              u4, __builtin_amdgcn_raw_buffer_load_b128(rws, 32 * lk + 16 * h, grp * 2048, 0));
+      }
+    };
+    struct WOp {
+      v8i b0, b1;
+    };
+    auto restore = [&](int p) __attribute__((always_inline)) {
+      const WRaw &r = w[p];
+      WOp B;
+      if constexpr (SEG <= 1) {
+        uint32_t d[6];
+        if constexpr (SEG == 0 && !FULL) {
+          const uint32_t f[3] = {r.q[0], r.q[1], r.z};
+          unfold3(f, d);
+        } else if constexpr (SEG == 1 && FULL) {
+          d[0] = r.p[0]; d[1] = r.p[1]; d[2] = r.p[2]; d[3] = r.p[3]; d[4] = r.q[0]; d[5] = r.q[1];
+        } else {
+          const uint32_t f[4] = {r.p[0], r.p[1], r.p[2], r.p[3]};
+          unfold4(f, d);
+        }
+        B.b0 = six(d);
+      } else if constexpr (SEG == 2) {
+        const uint32_t fl[4] = {r.p[0], r.p[1], r.p[2], r.p[3]};
+        uint32_t L[6], H[6];
+        unfold4(fl, L);
+        if constexpr (FULL) {
+          const uint32_t fh[4] = {r.h[0], r.h[1], r.h[2], r.h[3]};
+          unfold4(fh, H);
+        } else {
+          const uint32_t fh[2] = {r.q[0], r.q[1]};
+          unfold2(fh, L, H);
+        }
+        B.b0 = six(H);
+        B.b1 = six(L);
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          B.b0[k] = B.b0[4 + k] = (int)hi_codes<FULL>(r.p[k]);
+          B.b1[k] = B.b1[4 + k] = (int)lo_codes<FULL>(r.p[k]);
+        }
+      }
+      return B;
+    };
+    // (the scale bytes as in gemm_prefill_kernel: the weight dwords shifted by
+    // 8 hx, so that slab 2 tn + hx is byte 2 (tn & 1) of dword 2 k + tn / 2)
+    auto products = [&](auto k_tag, const v8i (&x)[TM][2], int p, const WOp &B)
+                        __attribute__((always_inline)) {
+      constexpr int K = decltype(k_tag)::v;
+      const int tn = p >> 1, c = p & 1;
+      const uint32_t wd = sc[0].w[c][K >> 1][2 * (K & 1) + (tn >> 1)];
+      if constexpr (SEG <= 1) {
+        constexpr int FB = SEG == 0 ? kFmtE2M3 : kFmtE3M2;
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+          acc[tm][tn] = (tn & 1)
+              ? mma<kFmtE3M2, FB, K, 2>(x[tm][c], B.b0, acc[tm][tn], sc[0].a[tm][c], wd)
+              : mma<kFmtE3M2, FB, K, 0>(x[tm][c], B.b0, acc[tm][tn], sc[0].a[tm][c], wd);
+      } else {
+        constexpr int F = SEG == 2 ? kFmtE3M2 : kFmtE4M3;
+        const uint32_t e = (wd >> (16 * (tn & 1))) & 0xFFu;
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+          acc[tm][tn] = mma<F, F, K, 0>(x[tm][c], B.b0, acc[tm][tn], sc[0].a[tm][c],
+                                        sat_plus<SEG == 2 ? 3 : 4>(e));
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+          acc[tm][tn] = mma<F, F, K, 0>(x[tm][c], B.b1, acc[tm][tn], sc[0].a[tm][c], e);
+      }
+    };
+    auto step = [&](auto k_tag, int s) __attribute__((always_inline)) {
+      constexpr int K = decltype(k_tag)::v;
+      load_a(xa[(K + 1) & 1], s + 1);
+      if constexpr (K == 0) load_s(sc[1], s + kGroupSteps);
+      WOp B = restore(0);
+#pragma unroll
+      for (int p = 0; p < 8; ++p) {
+        load_w(s + 1, p);
+        __builtin_amdgcn_sched_barrier(0);
+        WOp Bn;
+        if (p < 7) Bn = restore(p + 1);
+        products(k_tag, xa[K & 1], p, B);
+        B = Bn;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto next_group = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) sc[0].a[tm][c] = sc[1].a[tm][c];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[0].w[c][h][i] = sc[1].w[c][h][i] >> (8 * hx);
+      }
+    };
+    load_s(sc[1], sb);
+    load_a(xa[0], sb);
+#pragma unroll
+    for (int p = 0; p < 8; ++p) load_w(sb, p);
+    int s = sb;
+    for (; s + 4 <= se; s += 4) {
+      next_group();
+      step(Int<0>{}, s);
+      step(Int<1>{}, s + 1);
+      step(Int<2>{}, s + 2);
+      step(Int<3>{}, s + 3);
+    }
+    if (s < se) {
+      next_group();
+      step(Int<0>{}, s);
+      if (s + 1 < se) step(Int<1>{}, s + 1);
+      if (s + 2 < se) step(Int<2>{}, s + 2);
+    }
+  };
+  run(Int<0>{});
+  run(Int<1>{});
+  run(Int<2>{});
+  run(Int<3>{});
+
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < 4; ++tn)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        red[wave][16 * tm + 4 * tn + q][lane] =
+            v4f{acc[tm][tn][4 * q], acc[tm][tn][4 * q + 1], acc[tm][tn][4 * q + 2],
+                acc[tm][tn][4 * q + 3]};
+  __syncthreads();
+  const bool vec = (g.ldy & 3) == 0 && ((uintptr_t)g.y & 15) == 0 && col0 + BN <= g.N;
+  const int j = l32 & 3;
+#pragma unroll
+  for (int i = 0; i < 16 * TM / KG; ++i) {
+    const int tq = wave * (16 * TM / KG) + i, tm = tq >> 4, tn = (tq >> 2) & 3, q = tq & 3;
+    v4f s = red[0][tq][lane];
+#pragma unroll
+    for (int k = 1; k < KG; ++k) s += red[k][tq][lane];
+    s = quad_transpose(s, j);
+    const int64_t row = row0 + 32 * tm + 8 * q + 4 * lh + j, col = col0 + ((tn * 32 + l32) & ~3);
+    if (row >= g.M) continue;
+    float *dst = g.y + row * g.ldy + col;
+    if (vec) {
+      __builtin_nontemporal_store(s, (v4f *)dst);
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (col + c < g.N) dst[c] = s[c];
+    }
+  }
+}
+
+template <bool FULL, int KG, int TM, bool ONCE>
+hipError_t go_split(const GemmArgs &a, hipStream_t stream) {
+  const int mtiles = (int)((a.M + 32 * TM - 1) / (32 * TM)), ntiles = (int)((a.N + BN - 1) / BN);
+  hipLaunchKernelGGL((gemm_split_kernel<FULL, KG, TM, ONCE>), dim3((unsigned)(mtiles * ntiles)),
+                     dim3(64 * KG), 0, stream, a, mtiles, ntiles, ntiles % 8 == 0 ? ntiles / 8 : 0);
+  return hipGetLastError();
+}
+
+// Which split of K a shape takes, by the workgroups its row tiles give.  Over
+// weights already read, and over copies not in the last-level cache, us
+// against the tiled (M > 64) and the streaming kernel (M <= 64):
+//   four shares of 32 rows while they fit one workgroup per CU:
+//     100 x 4096 x 4096 9.3, 9.3 (26.7, 26.4); 1024 x 8192 x 1024 16.0, 16.3
+//     (47, 47); 64 x 4096 x 4096 9.1, 9.6 (13.3, 15.4)
+//   four shares of 64 rows, one workgroup per CU: 333 x 4096 x 4000 13.4, 14.3
+//     (28.2, 27.9); 300 x 14336 x 4096 31.7, 37.0 (78, 83)
+//   two shares of 64 rows, two workgroups per CU: 1024 x 4096 x 4096 24.2, 24.1
+//     (29.0, 28.4); 300 x 8192 x 8192 33.9, 41.5 (47, 51)
+//   more workgroups than that: the tiled kernel (2048 x 4096 x 4096 41.6, two
+//     shares 49.7).
+// Up to 64 rows the streaming kernel keeps the shapes where its deeper
+// pipeline over few columns counts: at most 16 rows and fewer column tiles
+// than 3/4 of the CUs (16 x 4096 x 14336 over new weights 11.7, split 12.9), at
+// most 32 rows and 64 column tiles (24 x 8192 x 8192 15.1, 21.5), and long K (64
+// x 28672 x 8192 56, 62).  One row tile over weights of more than 64 MB reads
+// them past the caches: 16 x 8192 x 28672 over new weights 25.3 (28.0 through
+// the caches, 28.0 the streaming kernel).
+enum Split { kNoSplit, kSplit4x32, kSplit4x32Once, kSplit4x64, kSplit2x64 };
+Split split_for(const GemmArgs &a, int cus) {
+  const LGeo lg(a.n3, a.n4, a.n6, a.n8);
+  const int64_t nt = (a.N + BN - 1) / BN, u1 = (a.M + 31) / 32 * nt, u2 = (a.M + 63) / 64 * nt;
+  if (a.M <= 16 && 4 * nt < 3 * cus) return kNoSplit;
+  if (a.M > 16 && a.M <= MXQ_DECODE_MAX_M && (lg.nsteps > 160 || (a.M <= 32 && nt <= 64)))
+    return kNoSplit;
+  if (u1 <= cus) return a.M <= 32 && nt * a.w_super > (64 << 20) ? kSplit4x32Once : kSplit4x32;
+  return u2 <= cus ? kSplit4x64 : u2 <= 2 * cus ? kSplit2x64 : kNoSplit;
+}
+
 }  // namespace
+
+bool gemm_takes_split(const GemmArgs &a) { return split_for(a, device_cu_count()) != kNoSplit; }
 
 hipError_t launch_gemm_prefill(const GemmArgs &a, hipStream_t stream) {
   auto go = [&](auto fc, auto tc) {
@@ -618,6 +962,16 @@ hipError_t launch_gemm_prefill(const GemmArgs &a, hipStream_t stream) {
     hipLaunchKernelGGL((gemm_prefill_kernel<FULL, TM>), dim3((unsigned)(mtiles * ntiles)), dim3(NT),
                        0, stream, a, mtiles, ntiles, gm, gn);
   };
+  if (const Split v = split_for(a, device_cu_count()); v != kNoSplit) {
+    auto by_clamp = [&](auto fc) {
+      constexpr bool FULL = decltype(fc)::value;
+      if (v == kSplit4x32) return go_split<FULL, 4, 1, false>(a, stream);
+      if (v == kSplit4x32Once) return go_split<FULL, 4, 1, true>(a, stream);
+      if (v == kSplit4x64) return go_split<FULL, 4, 2, false>(a, stream);
+      return go_split<FULL, 2, 2, false>(a, stream);
+    };
+    return a.full ? by_clamp(std::true_type{}) : by_clamp(std::false_type{});
+  }
   // 128-row tiles when 256-row tiles would leave CUs without a workgroup
   // (measured at K = N = 4096: 29-33 us against 37-41 us for M = 65 to
   // 1024; 256-row tiles are faster from one workgroup per CU up).  The

@@ -81,6 +81,9 @@ hipError_t launch_quantize_act(const QuantArgs &args, hipStream_t s);
 int64_t quantize_act_lds(int64_t K, bool rmsnorm = false);   // bytes of a staged row
 // Compute units of the current device (256 if the query fails).
 int device_cu_count();
+// Whether launch_gemm_prefill splits K for this shape (also for M <= 64, which
+// else is launch_gemm_decode's).
+bool gemm_takes_split(const GemmArgs &args);
 hipError_t launch_gemm_prefill(const GemmArgs &args, hipStream_t s);
 hipError_t launch_gemm_partials(const GemmArgs &args, hipStream_t s);
 hipError_t launch_gemm_decode(const GemmArgs &args, hipStream_t s);
