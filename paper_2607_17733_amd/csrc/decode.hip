@@ -375,11 +375,15 @@ static int decode_waves(int64_t units, int cus) {
 }
 
 int device_cu_count() {
+  static std::atomic<int> known[64] = {};            // asked once per device
   int dev = 0, n = 0;
-  if (hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-    return n;
-  return 256;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  const bool keep = dev >= 0 && dev < 64;
+  if (keep && (n = known[dev].load(std::memory_order_relaxed)) > 0) return n;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+    return 256;
+  if (keep) known[dev].store(n, std::memory_order_relaxed);
+  return n;
 }
 
 hipError_t launch_gemm_decode(const GemmArgs &a, hipStream_t stream) {

@@ -26,6 +26,7 @@
 #include "mxq_device.h"
 #include "mxq_internal.h"
 #include <algorithm>
+#include <atomic>
 
 namespace mxq {
 
@@ -886,8 +887,16 @@ static hipError_t go_quantize(const QuantArgs &a, int64_t grid, int threads, int
                               hipStream_t stream) {
   const auto fn = a.ties_away ? quantize_act_kernel<true, MODE, PROD>
                               : quantize_act_kernel<false, MODE, PROD>;
-  (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kMaxLds);
+  // the LDS limit, once per kernel and device
+  static std::atomic<uint64_t> raised[2] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+  std::atomic<uint64_t> &mask = raised[a.ties_away != 0];
+  if (dev < 0 || dev > 63 || !(mask.load(std::memory_order_relaxed) >> dev & 1)) {
+    if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)kMaxLds) == hipSuccess && dev >= 0 && dev <= 63)
+      mask.fetch_or(uint64_t(1) << dev, std::memory_order_relaxed);
+  }
   hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(threads), (size_t)lds, stream, a);
   return hipGetLastError();
 }

@@ -100,11 +100,15 @@ def _size(v: int, what: str) -> int:
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle (of the current device, as
+    torch.cuda.current_stream(), without the 3 us of its Stream object)."""
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 class Format:
@@ -129,10 +133,31 @@ class Format:
         self._c = _Fmt(self.K, BLOCK, self.round, self.clamp, 0,
                        self.widths.ctypes.data_as(ctypes.c_void_p).value,
                        None if perm is None else perm.data_ptr())
+        self._ref = ctypes.byref(self._c)
+        self._of = None
+        self._unit = None
 
     @property
     def ref(self):
-        return ctypes.byref(self._c)
+        return self._ref
+
+    def _units(self):
+        """What every size is a multiple of: the bytes of a 16-row activation
+        tile and its scales, a 128-column weight super-slab and its scales, a
+        packed row, an exponent row.  Asked of the library once per width map:
+        a serving loop checks its buffers on every call."""
+        w = self.widths.tobytes()
+        if w != self._of:
+            L, r = lib(), self._ref
+            self._unit = tuple(_size(v, name) for v, name in (
+                (L.mxq_act_bytes(r, 1), "mxq_act_bytes"),
+                (L.mxq_act_exp_bytes(r, 1), "mxq_act_exp_bytes"),
+                (L.mxq_weight_bytes(r, 1), "mxq_weight_bytes"),
+                (L.mxq_weight_exp_bytes(r, 1), "mxq_weight_exp_bytes"),
+                (L.mxq_act_packed_bytes(r), "mxq_act_packed_bytes"),
+                (L.mxq_exp_row_bytes(r), "mxq_exp_row_bytes")))
+            self._of = w
+        return self._unit
 
     @property
     def nb(self) -> int:
@@ -140,25 +165,33 @@ class Format:
 
     def act_packed_bytes(self) -> int:
         """Bytes of one packed activation row."""
-        return _size(lib().mxq_act_packed_bytes(self.ref), "mxq_act_packed_bytes")
+        return self._units()[4]
 
     def exp_row_bytes(self) -> int:
         """Bytes of one row of block exponents."""
-        return _size(lib().mxq_exp_row_bytes(self.ref), "mxq_exp_row_bytes")
+        return self._units()[5]
 
     def act_bytes(self, M: int) -> int:
         """The activation operand image of M rows (mxq_quantize_act)."""
-        return _size(lib().mxq_act_bytes(self.ref, M), "mxq_act_bytes")
+        if M < 0:
+            _check(2, "mxq_act_bytes")
+        return (M + 15) // 16 * self._units()[0]
 
     def act_exp_bytes(self, M: int) -> int:
         """Its scale bytes."""
-        return _size(lib().mxq_act_exp_bytes(self.ref, M), "mxq_act_exp_bytes")
+        if M < 0:
+            _check(2, "mxq_act_exp_bytes")
+        return (M + 15) // 16 * self._units()[1]
 
     def weight_bytes(self, N: int) -> int:
-        return _size(lib().mxq_weight_bytes(self.ref, N), "mxq_weight_bytes")
+        if N < 0:
+            _check(2, "mxq_weight_bytes")
+        return (N + 127) // 128 * self._units()[2]
 
     def weight_exp_bytes(self, N: int) -> int:
-        return _size(lib().mxq_weight_exp_bytes(self.ref, N), "mxq_weight_exp_bytes")
+        if N < 0:
+            _check(2, "mxq_weight_exp_bytes")
+        return (N + 127) // 128 * self._units()[3]
 
 
 def _bf16_2d(t, K, what):
@@ -173,7 +206,7 @@ def _bf16_2d(t, K, what):
 
 def _dev_bytes(t, n: int, what: str, dev=None):
     """A contiguous uint8 device tensor of at least n bytes (on `dev`)."""
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.uint8
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is torch.uint8
             and t.is_contiguous()):
         raise MxqError("%s must be a contiguous uint8 device tensor" % what)
     if t.numel() < n:

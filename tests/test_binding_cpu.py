@@ -158,3 +158,25 @@ def test_static_attention_rejects_oversize_on_the_host():
                                     fake, fake, fake, fake, fake, None)
     assert st == 8
     assert b"static scratch" in lib.mxq_status_str(8)
+
+
+def test_sizes_follow_the_library():
+    """The sizes a Format derives from one query of each unit equal the
+    library's for every count, also after its width map changed in place."""
+    lib = mxq.lib()
+    for widths in ([4], [3, 4, 6, 8], [4] * 6 + [6, 8], [8] * 5):
+        fmt = mxq.Format(32 * len(widths), widths)
+        for w in (None, 8):
+            if w:
+                fmt.widths[:] = w
+            for n in (0, 1, 16, 17, 127, 128, 129, 4000):
+                assert fmt.act_bytes(n) == lib.mxq_act_bytes(fmt.ref, n)
+                assert fmt.act_exp_bytes(n) == lib.mxq_act_exp_bytes(fmt.ref, n)
+                assert fmt.weight_bytes(n) == lib.mxq_weight_bytes(fmt.ref, n)
+                assert fmt.weight_exp_bytes(n) == lib.mxq_weight_exp_bytes(fmt.ref, n)
+            assert fmt.act_packed_bytes() == lib.mxq_act_packed_bytes(fmt.ref)
+            assert fmt.exp_row_bytes() == lib.mxq_exp_row_bytes(fmt.ref)
+    with pytest.raises(mxq.MxqError, match="shape"):
+        fmt.act_bytes(-1)
+    with pytest.raises(mxq.MxqError, match="width"):
+        mxq.Format(64, [6, 4]).weight_bytes(1)
