@@ -211,8 +211,10 @@ void gemm_prefill_kernel(GemmArgs g, int mtiles, int ntiles, int gm, int gn) {
       (int)min((last + 1 - ta) * g.a_tile, (int64_t)0x7fffffff), 0x00020000);
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
       (void *)(g.a_exp + ta * g.a_tile_sc), 0, 0x7fffffff, 0x00020000);
+  // (ends at the super-slab's end: a stage always loads kPieces pieces, which
+  // past the last step's chunks read zeros)
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-      (void *)(g.w_mant + (int64_t)nt * g.w_super), 0, 0x7fffffff, 0x00020000);
+      (void *)(g.w_mant + (int64_t)nt * g.w_super), 0, (int)g.w_super, 0x00020000);
   const __amdgpu_buffer_rsrc_t rws = __builtin_amdgcn_make_buffer_rsrc(
       (void *)(g.w_exp + (int64_t)nt * g.w_super_sc), 0, 0x7fffffff, 0x00020000);
   // The lane (lh, x) of a 32-wide tile reads, for K-chunk c, lane
@@ -255,30 +257,29 @@ void gemm_prefill_kernel(GemmArgs g, int mtiles, int ntiles, int gm, int gn) {
   };
   auto a_off = [&](int st) __attribute__((always_inline)) {
     // 24-byte lanes before the 8-bit segment, 32-byte lanes in it
-    return kLanes * (24 * min(st, lg.st0[3]) + 32 * max(st - lg.st0[3], 0));
+    return kLanes * (24 * st + 8 * max(st - lg.st0[3], 0));
   };
   auto w_off = [&](int st) __attribute__((always_inline)) {
-    return kWSlabs * (CB0 * dseg(st, 0) + CB1 * dseg(st, 1) + CB2 * dseg(st, 2) +
-                      CB3 * max(st - lg.st0[3], 0));
-  };
-  auto w_pieces = [&](int st) __attribute__((always_inline)) {
-    int cb = CB0;
-    cb = st >= lg.st0[1] ? CB1 : cb;
-    cb = st >= lg.st0[2] ? CB2 : cb;
-    cb = st >= lg.st0[3] ? CB3 : cb;
-    return cb * kWSlabs / 1024;
+    // every step as an 8-bit one, less what the others are shorter (half the
+    // scalar instructions of a sum over the segments, and no piece count to
+    // clamp to: gate / up at 4096 rows 290 -> 281 us, 2048 x 4096 x 4096 41.6 -> 40.6)
+    int o = CB3 * st;
+    if (CB0 != CB3) o += (CB0 - CB3) * min(st, lg.S[0]);
+    if (CB1 != CB3) o += (CB1 - CB3) * dseg(st, 1);
+    if (CB2 != CB3) o += (CB2 - CB3) * dseg(st, 2);
+    return kWSlabs * o;
   };
 
   // Weight loads of step st (clamped to the last) into its stage: pieces
-  // n = 0 .. kPieces - 1 of 1 KB (pieces past the step's chunk bytes repeat
-  // its last piece); wave w issues n = w + 4 j for j in [j0, j1).
+  // n = 0 .. kPieces - 1 of 1 KB (past a shorter step's chunks, bytes of the
+  // next step that nothing reads); wave w issues n = w + 4 j for j in [j0, j1).
   auto issue_w = [&](int st, int j0, int j1) __attribute__((always_inline)) {
     st = min(st, nsteps - 1);
-    const int wo = w_off(st), np = w_pieces(st);
+    const int wo = w_off(st);
     char *stage = ring + (st & (kWStages - 1)) * C::kStage;
 #pragma unroll
     for (int j = j0; j < j1; ++j) {
-      const int kb = min(wave + kWaves * j, np - 1);
+      const int kb = wave + kWaves * j;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(stage + kb * 1024), 16, lane * 16,
                                                wo + kb * 1024, 0, 0);
     }
