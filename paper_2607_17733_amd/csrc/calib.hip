@@ -123,7 +123,7 @@ __device__ inline double sort_key(double v) { return v != v ? __builtin_inf() : 
 // time with all of them.  The compare leaves a lane mask, whose population
 // count is scalar work, so a (column, 64 j) pair costs one vector
 // instruction: the rank of K columns is K^2 / 64 compares spread over
-// K / kRankCols workgroups (K = 4096: 12.4 us; one thread per column, sixteen
+// K / kRankCols workgroups (K = 4096: 8.9 us; one thread per column, sixteen
 // workgroups walking all K keys, took 310 us).
 constexpr int kRankCols = 16;
 
@@ -143,21 +143,32 @@ __global__ __launch_bounds__(kCalThreads) void rank_perm_kernel(const double *__
     before[c] = 0;
   }
   // 64 columns from j0: all of them before the workgroup's columns (equal
-  // sensitivities sort first), all after, or mixed
-  for (int64_t j0 = 64 * wave; j0 < K; j0 += kCalThreads) {
-    const int64_t j = j0 + lane;
-    const bool in = j < K;
-    const double sj = in ? sort_key(s[j]) : -__builtin_inf();   // not before any column
-    if (j0 + 64 <= i0) {
+  // sensitivities sort first), all after, or mixed.  The loads of eight such
+  // sets are issued together: one after the other they were most of the time.
+  constexpr int kPre = 8;
+  for (int64_t jb = 64 * wave; jb < K; jb += kPre * kCalThreads) {
+    double raw[kPre];
 #pragma unroll
-      for (int c = 0; c < kRankCols; ++c) before[c] += __popcll(__ballot(sj >= key[c]));
-    } else if (j0 >= i0 + kRankCols) {
+    for (int u = 0; u < kPre; ++u) {
+      const int64_t j = jb + u * kCalThreads + lane;
+      raw[u] = s[j < K ? j : K - 1];
+    }
 #pragma unroll
-      for (int c = 0; c < kRankCols; ++c) before[c] += __popcll(__ballot(sj > key[c]));
-    } else {
+    for (int u = 0; u < kPre; ++u) {
+      const int64_t j0 = jb + u * kCalThreads, j = j0 + lane;
+      const bool in = j < K;
+      const double sj = in ? sort_key(raw[u]) : -__builtin_inf();   // not before any column
+      if (j0 + 64 <= i0) {
 #pragma unroll
-      for (int c = 0; c < kRankCols; ++c)
-        before[c] += __popcll(__ballot(in && (sj > key[c] || (sj == key[c] && j < i0 + c))));
+        for (int c = 0; c < kRankCols; ++c) before[c] += __popcll(__ballot(sj >= key[c]));
+      } else if (j0 >= i0 + kRankCols) {
+#pragma unroll
+        for (int c = 0; c < kRankCols; ++c) before[c] += __popcll(__ballot(sj > key[c]));
+      } else {
+#pragma unroll
+        for (int c = 0; c < kRankCols; ++c)
+          before[c] += __popcll(__ballot(in && (sj > key[c] || (sj == key[c] && j < i0 + c))));
+      }
     }
   }
 #pragma unroll
