@@ -546,9 +546,13 @@ __device__ void rms_normalise(const QuantArgs &q, uint8_t *smem, int R, int rowB
                               int nthr, int64_t r0) {
   const int K = (int)q.K, nbk = K / kBlock;
   double *part = (double *)(smem + R * rowB);
-  float *rr = (float *)(part + R * nbk);
+  // (an odd count of sums per row, and lanes over rows first: a wave's reads of
+  // the rows, and the rows' serial sums below, then lie in distinct banks: 2048 x
+  // 4096 15.3 -> 14.7 us)
+  const int pst = nbk | 1;
+  float *rr = (float *)(part + R * pst);
   for (int it = t; it < R * nbk; it += nthr) {
-    const int lr = it / nbk, b = it - lr * nbk;
+    const int lr = it & (R - 1), b = it >> q.lg_rows;
     const u4 *xr = (const u4 *)(smem + lr * rowB + 64 * b);
     double sum = 0.0;
 #pragma unroll
@@ -561,13 +565,13 @@ __device__ void rms_normalise(const QuantArgs &q, uint8_t *smem, int R, int rowB
         sum += hi * hi;
       }
     }
-    part[it] = sum;
+    part[lr * pst + b] = sum;
   }
   __syncthreads();
   if (t < R) {
     // the block sums in order; loaded sixteen at a time so that only the
     // additions form the dependent chain
-    const double *pp = part + t * nbk;
+    const double *pp = part + t * pst;
     double acc = 0.0;
     int b = 0;
     for (; b + 16 <= nbk; b += 16) {
@@ -648,7 +652,7 @@ __global__ __launch_bounds__(kMaxThreads) void quantize_act_kernel(QuantArgs q) 
   int64_t w0 = blockIdx.x;
   if ((nwg & 7) == 0) w0 = (w0 & 7) * (nwg >> 3) + (w0 >> 3);
 
-  const int rms = PROD == kProdRms ? R * (8 * (K / kBlock) + 4) : 0;
+  const int rms = PROD == kProdRms ? R * (8 * (K / kBlock | 1) + 4) : 0;
   uint16_t *silu = nullptr;
   if (PROD == kProdSwiglu && q.silu_table) {
     silu = (uint16_t *)(smem + ((R * rowB + rms + 15) & ~15));
@@ -846,7 +850,7 @@ __global__ __launch_bounds__(kRowsThreads) void quantize_rows_kernel(QuantArgs q
 // Bytes per staged row: the row and its zero padding, plus with RMS
 // normalisation its block sums and its 1/rms.
 static int64_t row_lds(int64_t K, bool rmsnorm) {
-  return 2 * (K + kRowPad) + (rmsnorm ? 8 * (K / kBlock) + 4 : 0);
+  return 2 * (K + kRowPad) + (rmsnorm ? 8 * (K / kBlock | 1) + 4 : 0);
 }
 
 // Row groups: R rows (a power of two) and T threads per workgroup.  While one
