@@ -432,7 +432,7 @@ mxq_status mxq_peak_mfma(int kind, int64_t iters, float *sink, int64_t *ops,
  *   o[b][h][d] = sum_t softmax(s)_t * V[b][t][k][d],
  * where K and V are the dequantized cache values q * 2^(E - 127 - (m - 2)).
  * Arithmetic is float32: each block's dot product, then its scale; an
- * online softmax over chunks of 64 tokens; partial results merged in a
+ * online softmax over chunks of 32 tokens; partial results merged in a
  * fixed order, so repeated calls give identical results.
  *   fmt     the cache format: K = 128 (the head dimension), perm NULL,
  *           widths as for mxq_quantize_act (round and clamp do not matter

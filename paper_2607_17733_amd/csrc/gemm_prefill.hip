@@ -923,8 +923,8 @@ hipError_t go_split(const GemmArgs &a, hipStream_t stream) {
 //   more workgroups than that: the tiled kernel (2048 x 4096 x 4096 41.6, two
 //     shares 49.7).
 // Up to 64 rows the streaming kernel keeps the shapes where its deeper
-// pipeline over few columns counts: at most 16 rows and fewer column tiles
-// than 3/4 of the CUs (16 x 4096 x 14336 over new weights 11.7, split 12.9), at
+// pipeline counts: at most 16 rows and column tiles for fewer than 3/4 of the
+// CUs (16 x 4096 x 14336 over new weights 11.7, split 12.9) or more than all, at
 // most 32 rows and 64 column tiles (24 x 8192 x 8192 15.1, 21.5), and long K (64
 // x 28672 x 8192 56, 62).  One row tile over weights of more than 64 MB reads
 // them past the caches: 16 x 8192 x 28672 over new weights 25.3 (28.0 through
@@ -933,7 +933,7 @@ enum Split { kNoSplit, kSplit4x32, kSplit4x32Once, kSplit4x64, kSplit2x64 };
 Split split_for(const GemmArgs &a, int cus) {
   const LGeo lg(a.n3, a.n4, a.n6, a.n8);
   const int64_t nt = (a.N + BN - 1) / BN, u1 = (a.M + 31) / 32 * nt, u2 = (a.M + 63) / 64 * nt;
-  if (a.M <= 16 && 4 * nt < 3 * cus) return kNoSplit;
+  if (a.M <= 16 && (4 * nt < 3 * cus || nt > cus)) return kNoSplit;
   if (a.M > 16 && a.M <= MXQ_DECODE_MAX_M && (lg.nsteps > 160 || (a.M <= 32 && nt <= 64)))
     return kNoSplit;
   if (u1 <= cus) return a.M <= 32 && nt * a.w_super > (64 << 20) ? kSplit4x32Once : kSplit4x32;

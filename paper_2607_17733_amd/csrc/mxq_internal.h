@@ -36,7 +36,7 @@ struct QuantArgs {
   int weights;             // the weight layout (the rows are weight columns)
   int64_t w_super, w_super_sc;  // its bytes per 128-column super-slab
   int vec16;               // 16-byte source loads are aligned
-  int lg_rows;             // activations: log2 of the rows per group
+  int lg_rows;             // log2 of the rows per group
   int silu_table;          // SiLU(gate) from a table in LDS
   // activations: RMS-normalise each row before quantizing (y = g * x / rms)
   int rmsnorm;
