@@ -11,8 +11,8 @@
 // column: a sample's rows are summed in row order from zero (every square of
 // a bf16 value is exact in float64), and the sample's sum is then added to
 // the running total.  The row order makes each column one serial chain of
-// float64 additions, so the parallelism is columns x samples: one wave per
-// 64 columns and sample, all samples of a call in one launch.  The sort is by
+// float64 additions, so the parallelism is columns x samples: one lane per
+// column and sample, all samples of a call in one launch.  The sort is by
 // counting: a column's rank is the number of columns that sort before it
 // (larger sensitivity, or equal with a lower index; a NaN counts as +inf),
 // which fixes a unique order without a parallel sort.  The rank then places
@@ -25,8 +25,6 @@ namespace mxq {
 namespace {
 
 constexpr int kCalThreads = 256;
-constexpr int kColLanes = 64;       // columns of a wave
-constexpr int kRowBatch = 32;       // rows in flight while as many are summed
 
 __device__ inline double bf16_to_f64(uint16_t v) {
   return (double)__uint_as_float((uint32_t)v << 16);
@@ -51,53 +49,57 @@ __device__ inline const uint16_t *sample_ptr(const SampleBatch &b, int i) {
 __device__ inline int64_t sample_rows(const SampleBatch &b, int) { return b.nrows; }
 __device__ inline int64_t sample_ld(const SampleBatch &b, int) { return b.lead; }
 
-// One wave per 64 columns (blockIdx.x) and sample (blockIdx.y): the column
-// sums of the sample in row order, to its row of `out` (or added to it).
-// With the samples in one launch the kernel is bound by the HBM read; a wave
-// keeps the next 32 rows in flight while it sums the current 32 (64 loads,
-// the most a wave can count).  Sixteen samples of 2048 x 4096 (268 MB): 43.5 us
-// (6.2 TB/s); a launch per sample, whose 64 waves are a sixteenth of the
-// GPU's SIMDs, took 98 us each.
-template <class Samples>
-__global__ __launch_bounds__(kColLanes) void colsq_kernel(Samples sm, int64_t K, double *out,
-                                                          int accumulate) {
+// A lane per column, COLS columns per workgroup (blockIdx.x) and sample
+// (blockIdx.y): the column sums of the sample in row order, to its row of
+// `out` (or added to it).  A wave keeps the next BATCH rows in flight while it
+// sums the current ones.  The kernel is bound by the HBM read once enough rows
+// are in flight: few waves need 32 each (64 loads, the most a wave can count),
+// and one wave per workgroup to spread over the CUs; more than 8 per CU do with
+// 4 each, and workgroups of 256 adjacent columns read longer runs.  Sixteen
+// samples of 2048 x 4096 (268 MB): 43.5 us (6.2 TB/s; a launch per sample, whose
+// 64 waves are a sixteenth of the GPU's SIMDs, took 98 us each, a batch with 8
+// rows in flight 107); 128 samples 388 us with 4 rows, 401 with 32, 449 with 32
+// and 64 columns per workgroup.
+template <class Samples, int COLS, int BATCH>
+__global__ __launch_bounds__(COLS) void colsq_kernel(Samples sm, int64_t K, double *out,
+                                                     int accumulate) {
   const int y = blockIdx.y;
-  const int64_t k = (int64_t)blockIdx.x * kColLanes + threadIdx.x;
+  const int64_t k = (int64_t)blockIdx.x * COLS + threadIdx.x;
   const int64_t rows = sample_rows(sm, y), ld = sample_ld(sm, y);
   if (k >= K) return;
   const uint16_t *p = sample_ptr(sm, y) + k;
   double sum = 0.0;
-  auto fetch = [&](uint16_t (&v)[kRowBatch], int64_t r) __attribute__((always_inline)) {
+  auto fetch = [&](uint16_t (&v)[BATCH], int64_t r) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kRowBatch; ++u) v[u] = p[(r + u) * ld];
+    for (int u = 0; u < BATCH; ++u) v[u] = p[(r + u) * ld];
   };
-  auto add = [&](const uint16_t (&v)[kRowBatch]) __attribute__((always_inline)) {
+  auto add = [&](const uint16_t (&v)[BATCH]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kRowBatch; ++u) {
+    for (int u = 0; u < BATCH; ++u) {
       const double d = bf16_to_f64(v[u]);
       sum += d * d;
     }
   };
   int64_t r = 0;
-  const int64_t nb = rows / kRowBatch;
+  const int64_t nb = rows / BATCH;
   if (nb > 0) {
-    uint16_t a[kRowBatch], b[kRowBatch];
+    uint16_t a[BATCH], b[BATCH];
     fetch(a, 0);
     int64_t i = 1;
     for (; i + 1 < nb; i += 2) {
-      fetch(b, i * kRowBatch);
+      fetch(b, i * BATCH);
       add(a);
-      fetch(a, (i + 1) * kRowBatch);
+      fetch(a, (i + 1) * BATCH);
       add(b);
     }
     if (i < nb) {
-      fetch(b, i * kRowBatch);
+      fetch(b, i * BATCH);
       add(a);
       add(b);
     } else {
       add(a);
     }
-    r = nb * kRowBatch;
+    r = nb * BATCH;
   }
   for (; r < rows; ++r) {
     const double d = bf16_to_f64(p[r * ld]);
@@ -191,9 +193,14 @@ __global__ __launch_bounds__(kCalThreads) void rank_perm_kernel(const double *__
 template <class Samples>
 hipError_t go_colsq(const Samples &sm, int64_t n, int64_t K, double *out, bool accumulate,
                     hipStream_t stream) {
-  const int64_t blocks = (K + kColLanes - 1) / kColLanes;
-  hipLaunchKernelGGL(colsq_kernel<Samples>, dim3((unsigned)blocks, (unsigned)n), dim3(kColLanes), 0,
-                     stream, sm, K, out, accumulate ? 1 : 0);
+  auto launch = [&](auto fn, int cols) {
+    hipLaunchKernelGGL(fn, dim3((unsigned)((K + cols - 1) / cols), (unsigned)n), dim3(cols), 0,
+                       stream, sm, K, out, accumulate ? 1 : 0);
+  };
+  if ((K + 63) / 64 * n <= 8 * (int64_t)device_cu_count())
+    launch(colsq_kernel<Samples, 64, 32>, 64);
+  else
+    launch(colsq_kernel<Samples, 256, 4>, 256);
   return hipGetLastError();
 }
 

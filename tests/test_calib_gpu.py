@@ -126,3 +126,15 @@ def test_samples_of_mixed_width_are_summed_one_by_one():
     perm, _ = mxq.calibrate([a, b], 0.5, 0.2)
     s = mxq.calib_colsq(b, mxq.calib_colsq(a), accumulate=True)
     assert torch.equal(perm, mxq.calib_perm(s, *mxq.calib_counts(128, 0.2, 0.5)[1:]))
+
+
+def test_many_samples_take_wide_workgroups():
+    """More than 8 waves per CU (2048 on 256 CUs): 256 columns per workgroup,
+    four rows in flight; columns past the last workgroup's end, row counts on
+    both sides of a batch."""
+    say("calib-wide")
+    for rows in (3, 8, 13):
+        n, K = 130, 1056                                 # 130 x 17 waves
+        samples = _samples(rows, n, rows, K)
+        s = mxq.calib_colsq_samples(torch.stack([to_dev_bf16(b) for b in samples]))
+        assert np.array_equal(s.cpu().numpy(), calib.column_sensitivity(samples))
