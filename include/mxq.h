@@ -430,7 +430,9 @@ mxq_status mxq_peak_mfma(int kind, int64_t iters, float *sink, int64_t *ops,
  * for sequence b and query head h, with KV head k = h / G (G = Hq / Hkv),
  *   s_t = scale * sum_d q[b][h][d] * K[b][t][k][d]   (t = 0..T-1),
  *   o[b][h][d] = sum_t softmax(s)_t * V[b][t][k][d],
- * where K and V are the dequantized cache values q * 2^(E - 127 - (m - 2)).
+ * where K and V are the dequantized cache values q * 2^(E - 127 - (m - 2)), for
+ * every E alike: a block that held an Inf or NaN has E = 255 and zero mantissas
+ * and counts as zeros (the GEMMs give NaN for it).
  * Arithmetic is float32: each block's dot product, then its scale; an
  * online softmax over chunks of 32 tokens; partial results merged in a
  * fixed order, so repeated calls give identical results.

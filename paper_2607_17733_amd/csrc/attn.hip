@@ -113,7 +113,7 @@ constexpr int kVRow = 2 * kD + 32;
 template <int N3, int N4, int N6, int N8>
 struct Geo {
   static constexpr bool kUniform = N3 == 4 || N4 == 4 || N6 == 4 || N8 == 4;
-  static constexpr int kN4 = N4;
+  static constexpr bool kBig = N3 < 4;       // blocks wider than 3 bits
   static constexpr int width(int b) {
     return b < N3 ? 3 : b < N3 + N4 ? 4 : b < N3 + N4 + N6 ? 6 : 8;
   }
@@ -202,10 +202,11 @@ __device__ inline bf8 to_bf8(const float (&x)[8]) {
   return r;
 }
 
-// A 4-bit block's scale for the FP8 conversion, 2^(E - 127 - 2 + 9): beyond
-// E = 247 it passes the float range, and the operand is scaled again
-// (big_blocks).  A block of E = 255 holds zeros.
-constexpr int kBigE = 247;
+// The largest exponent whose scale keeps an M-bit block's dequantization inside
+// the float range: the FP8 conversion of a 4-bit block takes 2^(E - 127 - 2 + 9),
+// and the offset of 6- and 8-bit blocks is -2^(E - 127 + 1).  Beyond it the block
+// is dequantized at this exponent and scaled again (big_blocks).
+constexpr int max_exp(int m) { return m == 3 ? 255 : m == 4 ? 247 : 253; }
 
 // Element of slot i of a lane's eight: 4- and 6-bit blocks yield the even
 // elements, then the odd ones.
@@ -224,7 +225,7 @@ __device__ inline bf8 dequant(const Raw<Gm> &r, int g) {
     const uint32_t sg = w & 0x88888888u, one = sg >> 3;
     const uint32_t mag = (w ^ ((one << 4) - one)) + one;
     const uint32_t ev = low_nibbles_else(mag, sg << 4), od = low_nibbles_else(mag >> 4, sg);
-    const float sc = __uint_as_float((uint32_t)(min(E, kBigE) + 7) << 23);
+    const float sc = __uint_as_float((uint32_t)(min(E, max_exp(4)) + 7) << 23);
     bf2 v[4];
     v[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(ev, sc, false);
     v[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(ev, sc, true);
@@ -232,7 +233,7 @@ __device__ inline bf8 dequant(const Raw<Gm> &r, int g) {
     v[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(od, sc, true);
     return bf8{v[0][0], v[0][1], v[1][0], v[1][1], v[2][0], v[2][1], v[3][0], v[3][1]};
   } else {
-    const float sc = __builtin_amdgcn_ldexpf(1.f, E - 127 - (M - 2));
+    const float sc = __builtin_amdgcn_ldexpf(1.f, (M == 3 ? E : min(E, max_exp(M))) - 127 - (M - 2));
     float x[8];
     if constexpr (M == 3) {
       uint32_t w;
@@ -246,7 +247,8 @@ __device__ inline bf8 dequant(const Raw<Gm> &r, int g) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) x[j] = (float)(int)__builtin_amdgcn_sbfe((int)w, 3 * j, 3) * sc;
     } else {
-      // bytes of q + 2^(M - 1); (u - 2^(M - 1)) sc is exact, in one rounding
+      // bytes of q + 2^(M - 1); u sc - 2^(M - 1) sc is exact, in one rounding
+      // (both terms are finite up to max_exp)
       uint32_t b0, b1;
       if constexpr (M == 8) {
         b0 = r.w[Gm::kUniform ? 2 * J : S] ^ 0x80808080u;
@@ -271,25 +273,27 @@ __device__ inline bf8 dequant(const Raw<Gm> &r, int g) {
   }
 }
 
-// Whether one of the 4-bit blocks of a row has an exponent above kBigE = 247,
-// i.e. its top five bits set (a block of E = 255 among them).
+// Whether a block of a row may have an exponent above max_exp, i.e. its top
+// five bits set (E >= 248).
 template <class Gm>
 __device__ inline bool has_big(uint32_t ex) {
   uint32_t m = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
-    if (Gm::width(j) == 4) m |= 0x20u << (8 * j);
+    if (Gm::width(j) != 3) m |= 0x20u << (8 * j);
   return ((((ex >> 3) & 0x1F1F1F1Fu) + 0x01010101u) & m) != 0;
 }
 
-// The rest of such blocks' scales.
+// The rest of such blocks' scales.  E = 255 is no exception: the quantizer
+// writes zero mantissas with it, which stay zeros.
 template <class Gm>
 __device__ inline void big_blocks(const Raw<Gm> &r, int g, bf8 (&v)[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    if (Gm::width(j) != 4) continue;
+    const int m = Gm::width(j);
+    if (m == 3) continue;
     const int E = (int)((r.ex >> (8 * (Gm::kUniform ? g : j))) & 255u);
-    const float f = E > kBigE && E < 255 ? __builtin_amdgcn_ldexpf(1.f, E - kBigE) : 1.f;
+    const float f = __builtin_amdgcn_ldexpf(1.f, max(E - max_exp(m), 0));
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[j][i] = (__bf16)((float)v[j][i] * f);
   }
@@ -301,7 +305,7 @@ __device__ inline void dequant_row(const Raw<Gm> &r, int g, bool big, bf8 (&v)[4
   v[1] = dequant<Gm, 1>(r, g);
   v[2] = dequant<Gm, 2>(r, g);
   v[3] = dequant<Gm, 3>(r, g);
-  if (Gm::kN4 > 0 && big) big_blocks(r, g, v);
+  if (Gm::kBig && big) big_blocks(r, g, v);
 }
 
 // e^d for d <= kSlack: 2^t with t = d log2 e, and what t lost in rounding (d -
@@ -433,7 +437,7 @@ void attn_decode_kernel(AttnArgs a) {
       }
     }
     xs[wave][lane >> 5][lane & 31] = px;
-    const bool big = Gm::kN4 > 0 && __any(has_big<Gm>(px));
+    const bool big = Gm::kBig && __any(has_big<Gm>(px));
     wave_sync();
     if constexpr (!Gm::kUniform) {
       if (c0 + kChunk * nw < t1) fetch(c0 + kChunk * nw);

@@ -1,5 +1,5 @@
 """Decode attention at the edges of its arithmetic against the float64 oracle:
-block exponents past the scaled conversion's range, a negative score scale,
+block exponents up to the largest, a negative score scale,
 heads that fill one or both halves of the score tile, chunks that end in
 either half."""
 import numpy as np
@@ -45,3 +45,63 @@ def test_attention_edges(widths, G, T, kexp, vexp, scale):
         err = np.abs(o[b] - ref).max(axis=1) / vmax[np.arange(G * Hkv) // G]
         # scores of a few units in float32 (2^-22 relative) and float32 sums of T terms
         assert err.max() <= 1e-5, err.max()
+
+
+def _top_rows(g, rows, m, E, where):
+    """Cache rows whose block 2, in the rows of `where`, has exponent E: values of
+    every size down to zero below a largest one (E = 255: it holds an infinity);
+    the other blocks N(0, 1)."""
+    x = g.normal(size=(rows, 128)).astype(np.float32)
+    q = g.integers(-(2 ** (m - 1)) + 1, 2 ** (m - 1), size=(rows, 32)).astype(np.float64)
+    q[:, 5], q[:, 6], q[:, 9] = 2 ** (m - 1) - 1, 0, -(2 ** (m - 2))
+    lsb = np.ldexp(1.0, min(E, 254) - 127 - (m - 2))
+    top = (q * lsb).astype(np.float32)
+    if E == 255:
+        top[:, 9] = np.inf
+    x[where, 64:96] = top[where]
+    return _bits(x)
+
+
+@pytest.mark.parametrize("widths", [[6] * 4, [8] * 4, [4] * 4, [3, 4, 6, 8], [4, 6, 8, 8]])
+@pytest.mark.parametrize("E", [248, 253, 254, 255])
+@pytest.mark.parametrize("T", [1, 45])
+def test_attention_largest_exponents(widths, E, T):
+    """Blocks at the top of the exponent range, as K and as V: finite values at
+    E = 253 and 254, zeros where the quantizer met an infinity (E = 255)."""
+    say("attn-largest-exponents", widths, E, T)
+    B, G, Hkv, D = 1, 3, 2, 128
+    g = np.random.Generator(np.random.PCG64(E + T))
+    fmt = mxq.Format(D, widths)
+    top = np.zeros(T * Hkv, bool)
+    top[(T // 2) * Hkv:(T // 2 + 1) * Hkv] = True          # one token's rows: the sums stay finite
+
+    def check(q, kb, vb, scale):
+        qb = _bits(q)
+        o = mxq.attn_decode(to_dev_bf16(qb.reshape(-1, D)).reshape(B, G * Hkv, D),
+                            mxq.quantize_rows(to_dev_bf16(kb), fmt),
+                            mxq.quantize_rows(to_dev_bf16(vb), fmt), fmt, B, G * Hkv, Hkv, T, scale)
+        o = o.cpu().numpy().astype(np.float64)
+        kd, vd = oattn.dequantize_cache(kb, widths), oattn.dequantize_cache(vb, widths)
+        for d in (kd, vd):
+            np.nan_to_num(d, copy=False, nan=0.0)          # (the oracle's value of an E = 255 block)
+        ref = oattn.attention(W.bf16_bits_to_f32(qb).astype(np.float64), kd, vd, B, G * Hkv, Hkv,
+                              T, scale)
+        assert np.isfinite(o).all()
+        if T == 1:                                         # the token's own values
+            assert np.abs(o - ref).max() <= 1e-6 * np.abs(ref).max()
+            big = np.abs(ref) > 0
+            assert (np.abs(o - ref)[big] <= 1e-6 * np.abs(ref)[big]).all() and not o[~big].any()
+        for b in range(4):                                 # float32 sums of T terms, per block
+            s = slice(32 * b, 32 * b + 32)
+            lim = 1e-5 * np.abs(vd[:, s]).max()
+            assert np.abs(o[..., s] - ref[..., s]).max() <= lim
+
+    plain = _bits(g.normal(size=(T * Hkv, D)).astype(np.float32))
+    qn = g.normal(size=(B, G * Hkv, D))
+    # as V: scores of a few units
+    check(qn, plain, _top_rows(g, T * Hkv, widths[2], E, top), 0.05)
+    # as K: the queries bring the large block's scores down to a few units, the
+    # other blocks' to nothing
+    qs = qn.copy()
+    qs[..., 64:96] = np.ldexp(qs[..., 64:96], -120)
+    check(qs, _top_rows(g, T * Hkv, widths[2], E, top), plain, 1e-3)
