@@ -35,7 +35,9 @@
 // (the V operand takes its tokens in the same slots).  The softmax is online
 // against a reference m per head that is raised (and the sums rescaled) only
 // when a score passes it by more than kSlack: the probabilities are then up to
-// e^kSlack instead of 1, which costs float32 no precision.  Waves, then splits,
+// e^kSlack instead of 1, which costs float32 no precision.  It would cost
+// range: from the first block of E >= 224 on, a wave keeps m the largest score
+// (below that, sums of 2^31 / e^kSlack such tokens stay finite).  Waves, then splits,
 // are merged in a fixed order, so results do not depend on timing.  Each
 // width mix of the four blocks is its own instance, so block offsets and
 // widths are compile-time constants.
@@ -273,15 +275,10 @@ __device__ inline bf8 dequant(const Raw<Gm> &r, int g) {
   }
 }
 
-// Whether a block of a row may have an exponent above max_exp, i.e. its top
-// five bits set (E >= 248).
-template <class Gm>
+// Whether a block of a row has its top three exponent bits set (E >= 224): it
+// may pass max_exp, or, as V, leave the sums no room for kSlack.
 __device__ inline bool has_big(uint32_t ex) {
-  uint32_t m = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (Gm::width(j) != 3) m |= 0x20u << (8 * j);
-  return ((((ex >> 3) & 0x1F1F1F1Fu) + 0x01010101u) & m) != 0;
+  return (ex & (ex << 1) & (ex << 2) & 0x80808080u) != 0;
 }
 
 // The rest of such blocks' scales.  E = 255 is no exception: the quantizer
@@ -385,6 +382,7 @@ void attn_decode_kernel(AttnArgs a) {
   const int64_t t1 = t0 + a.tokens_per_split < a.T ? t0 + a.tokens_per_split : a.T;
   const float scale = fabsf(a.scale);                      // its sign is in Q
   float run_m = ninf, run_l = 0.f;                         // column n; this lane's tokens
+  float top = ninf, slack = kSlack;                        // the lane's largest score (unscaled)
   f4 o[8];                                                 // columns 4g + r, value 16 dt + n
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) o[dt] = (f4){0.f, 0.f, 0.f, 0.f};
@@ -437,7 +435,8 @@ void attn_decode_kernel(AttnArgs a) {
       }
     }
     xs[wave][lane >> 5][lane & 31] = px;
-    const bool big = Gm::kBig && __any(has_big<Gm>(px));
+    const bool big = __any(has_big(px));
+    if (big) slack = 0.f;                                  // for the rest of the wave's tokens
     wave_sync();
     if constexpr (!Gm::kUniform) {
       if (c0 + kChunk * nw < t1) fetch(c0 + kChunk * nw);
@@ -480,7 +479,6 @@ void attn_decode_kernel(AttnArgs a) {
       return (DUP ? (lower ? 0 : 16) : 16 * (i >> 2)) + 4 * g + (i & 3);
     };
     float p[kVals];
-    float cm = ninf;
 #pragma unroll
     for (int i = 0; i < kVals; ++i)
       p[i] = !DUP ? sacc[i >> 2][i & 3] : lower ? sacc[0][i] : sacc[1][i];
@@ -490,9 +488,9 @@ void attn_decode_kernel(AttnArgs a) {
         if (tok(i) >= nt) p[i] = ninf;
     }
 #pragma unroll
-    for (int i = 0; i < kVals; ++i) cm = fmaxf(cm, p[i]);
-    cm = cm == ninf ? ninf : cm * scale;
-    if (__any(cm > run_m + kSlack || run_m == ninf)) {
+    for (int i = 0; i < kVals; ++i) top = fmaxf(top, p[i]);
+    float cm = top == ninf ? ninf : top * scale;
+    if (__any(cm > run_m + slack || run_m == ninf)) {
       cm = fmaxf(cm, __shfl_xor(cm, 16));
       cm = fmaxf(cm, __shfl_xor(cm, 32));
       const float nm = fmaxf(run_m, cm);

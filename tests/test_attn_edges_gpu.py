@@ -105,3 +105,33 @@ def test_attention_largest_exponents(widths, E, T):
     qs = qn.copy()
     qs[..., 64:96] = np.ldexp(qs[..., 64:96], -120)
     check(qs, _top_rows(g, T * Hkv, widths[2], E, top), plain, 1e-3)
+
+
+def _run(fmt, q, k, v, B, Hq, Hkv, T, scale):
+    D = 128
+    qb, kb, vb = _bits(q), _bits(k), _bits(v)
+    o = mxq.attn_decode(to_dev_bf16(qb.reshape(-1, D)).reshape(B, Hq, D),
+                        mxq.quantize_rows(to_dev_bf16(kb.reshape(-1, D)), fmt),
+                        mxq.quantize_rows(to_dev_bf16(vb.reshape(-1, D)), fmt), fmt, B, Hq, Hkv, T,
+                        scale)
+    kd = oattn.dequantize_cache(kb.reshape(-1, D), fmt.widths)
+    vd = oattn.dequantize_cache(vb.reshape(-1, D), fmt.widths)
+    ref = oattn.attention(W.bf16_bits_to_f32(qb).astype(np.float64), kd, vd, B, Hq, Hkv, T, scale)
+    return o.cpu().numpy().astype(np.float64), ref, vd
+
+
+@pytest.mark.parametrize("widths", [[4] * 4, [3] * 4, [4, 4, 6, 8]])
+@pytest.mark.parametrize("G", [1, 9])
+def test_attention_large_values(widths, G):
+    """A head whose scores rise by 3.9 in a wave's second chunk, with values near
+    2^120: sums of probabilities up to 1 stay finite."""
+    say("attn-large-values", widths, G)
+    B, Hkv, T, D = 64, 8, 200, 128                         # one split: 4 waves of one or two chunks
+    g = np.random.Generator(np.random.PCG64(G))
+    q = np.zeros((B, G * Hkv, D))
+    q[..., 0] = 1.0
+    k = np.zeros((B, T, Hkv, D))
+    k[:, 128:160, :, 0] = 4.0                              # exact in every width
+    v = np.ldexp(g.uniform(1, 1.9, size=(B, T, Hkv, D)), 120)
+    o, ref, vd = _run(mxq.Format(D, widths), q, k, v, B, G * Hkv, Hkv, T, 3.9 / 4)
+    assert np.abs(o - ref).max() <= 1e-5 * np.abs(vd).max()
