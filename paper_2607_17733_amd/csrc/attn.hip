@@ -382,6 +382,7 @@ void attn_decode_kernel(AttnArgs a) {
   const int64_t t1 = t0 + a.tokens_per_split < a.T ? t0 + a.tokens_per_split : a.T;
   const float scale = fabsf(a.scale);                      // its sign is in Q
   float run_m = ninf, run_l = 0.f;                         // column n; this lane's tokens
+  float ref = 0.f;                                         // run_m, once finite
   float top = ninf, slack = kSlack;                        // the lane's largest score (unscaled)
   f4 o[8];                                                 // columns 4g + r, value 16 dt + n
 #pragma unroll
@@ -497,6 +498,7 @@ void attn_decode_kernel(AttnArgs a) {
       const float alpha = run_m == ninf ? 0.f : exp_f(run_m - nm);
       run_l *= alpha;
       run_m = nm;
+      ref = nm == ninf ? 0.f : nm;                         // scores of -inf weigh 0
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float ah = __shfl(alpha, 4 * g + r);         // column 4g + r lives in lane 4g + r
@@ -507,7 +509,7 @@ void attn_decode_kernel(AttnArgs a) {
     // the probabilities, as three bf16 terms summing to the float32 value
     float e[kVals];
 #pragma unroll
-    for (int i = 0; i < kVals; ++i) e[i] = exp_f(fmaf(p[i], scale, -run_m));
+    for (int i = 0; i < kVals; ++i) e[i] = exp_f(fmaf(p[i], scale, -ref));
     if (nt < kChunk) {
 #pragma unroll
       for (int i = 0; i < kVals; ++i)
@@ -566,7 +568,8 @@ void attn_decode_kernel(AttnArgs a) {
 #pragma unroll
     for (int v = 0; v < kWaves; ++v)
       if (v < nw) M = fmaxf(M, fmaxf(mm[v][c], mm[v][c ^ (kMaxG - kStride)]));
-    mf[w][c] = mm[w][c] == ninf ? 0.f : expf(mm[w][c] - M);     // no token of its own
+    // without a score above -inf: nothing (or a NaN, which stays)
+    mf[w][c] = mm[w][c] == ninf ? ml[w][c] : expf(mm[w][c] - M);
   }
   __syncthreads();
   float *mo = (float *)pool;                               // [kWaves][kMaxG][kD]
@@ -607,7 +610,8 @@ void attn_decode_kernel(AttnArgs a) {
           M = fmaxf(M, mm[w][k]);
           L += mf[w][k] == 0.f ? 0.f : ml[w][k] * mf[w][k];
         }
-    part[t * (kD + 2)] = M;
+    // (finite: the merge of the splits takes differences)
+    part[t * (kD + 2)] = fmaxf(M, -__FLT_MAX__);
     part[t * (kD + 2) + 1] = L;
   }
 }

@@ -135,3 +135,24 @@ def test_attention_large_values(widths, G):
     v = np.ldexp(g.uniform(1, 1.9, size=(B, T, Hkv, D)), 120)
     o, ref, vd = _run(mxq.Format(D, widths), q, k, v, B, G * Hkv, Hkv, T, 3.9 / 4)
     assert np.abs(o - ref).max() <= 1e-5 * np.abs(vd).max()
+
+
+@pytest.mark.parametrize("low", [range(16), range(0, 100), range(64, 160), range(16, 200)])
+def test_attention_scores_of_minus_infinity(low):
+    """Tokens whose scores overflow to -inf weigh nothing, also where they fill a
+    half chunk, a wave's first chunk or a split; a query with a NaN gives NaN."""
+    say("attn-minus-infinity", low)
+    g = np.random.Generator(np.random.PCG64(low.stop))
+    for B, G, Hkv, T in ((64, 2, 8, 200), (1, 9, 1, 200)):  # one split; splits of 64 tokens
+        D, widths = 128, [4, 4, 6, 8]
+        q = g.normal(size=(B, G * Hkv, D))
+        q[..., 0] = np.ldexp(1.0, 100)
+        k = g.normal(size=(B, T, Hkv, D))
+        k[..., 0] = 0.0
+        k[:, low, :, 0] = -np.ldexp(1.0, 40)               # 2^140 in float32
+        v = g.normal(size=(B, T, Hkv, D))
+        q[0, 1, 5] = np.nan
+        o, ref, vd = _run(mxq.Format(D, widths), q, k, v, B, G * Hkv, Hkv, T, 0.05)
+        assert np.isnan(o[0, 1]).all()
+        o[0, 1] = ref[0, 1] = 0.0
+        assert np.abs(o - ref).max() <= 1e-5 * np.abs(vd).max()
