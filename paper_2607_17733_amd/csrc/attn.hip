@@ -616,65 +616,72 @@ void attn_decode_kernel(AttnArgs a) {
   }
 }
 
-// o[b][h] = the splits' partials merged in a fixed order.  Eight groups of 32
-// lanes (four values each) take every eighth split, eight splits' loads in
-// flight together, so that up to 64 splits cost one memory latency; then the
-// groups are merged in order.
-constexpr int kCombGroups = 8, kCombBatch = 8, kCombThreads = kCombGroups * kD / 4;
+// o[b][h] = the splits' partials merged in a fixed order.  Groups of LPG lanes
+// (four values each, from column 4 LPG blockIdx.z) take every kGroups-th split,
+// BATCH splits' loads in flight together, so that kGroups * BATCH splits cost
+// one memory latency; then the groups are merged in order.
+constexpr int kCombThreads = 256;
 
+template <int LPG, int BATCH>
 __global__ __launch_bounds__(kCombThreads) void attn_combine_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float po[kCombGroups][kD];
-  __shared__ float pm[kCombGroups], pl[kCombGroups];
-  const int t = threadIdx.x, d = 4 * (t & 31), grp = t >> 5, h = blockIdx.x, b = blockIdx.y;
+  constexpr int kGroups = kCombThreads / LPG, kCols = 4 * LPG;
+  __shared__ __attribute__((aligned(16))) float po[kGroups][kCols];
+  __shared__ float pm[kGroups], pl[kGroups];
+  const int t = threadIdx.x, d = 4 * (t % LPG), grp = t / LPG, h = blockIdx.x, b = blockIdx.y;
+  const int c0 = kCols * blockIdx.z;
   const int G = a.G, kvh = h / G, g = h - kvh * G, S = a.splits;
   const float *base = a.work + (((int64_t)b * a.Hkv + kvh) * S * G + g) * (kD + 2);
   const int64_t stride = (int64_t)G * (kD + 2);
   const float ninf = -__builtin_inff();
   float M = ninf, L = 0.f;
   f4 O = {0.f, 0.f, 0.f, 0.f};
-  for (int s0 = grp; s0 < S; s0 += kCombGroups * kCombBatch) {
-    f2 ml[kCombBatch], o0[kCombBatch], o1[kCombBatch];
+  for (int s0 = grp; s0 < S; s0 += kGroups * BATCH) {
+    f2 ml[BATCH], o0[BATCH], o1[BATCH];
     float nm = M;
 #pragma unroll
-    for (int u = 0; u < kCombBatch; ++u) {
-      const float *p = base + min(s0 + kCombGroups * u, S - 1) * stride;
+    for (int u = 0; u < BATCH; ++u) {
+      const float *p = base + min(s0 + kGroups * u, S - 1) * stride;
       ml[u] = *(const f2 *)p;
-      o0[u] = *(const f2 *)(p + 2 + d);
-      o1[u] = *(const f2 *)(p + 4 + d);
+      o0[u] = *(const f2 *)(p + 2 + c0 + d);
+      o1[u] = *(const f2 *)(p + 4 + c0 + d);
     }
 #pragma unroll
-    for (int u = 0; u < kCombBatch; ++u)
-      if (s0 + kCombGroups * u < S) nm = fmaxf(nm, ml[u][0]);
+    for (int u = 0; u < BATCH; ++u)
+      if (s0 + kGroups * u < S) nm = fmaxf(nm, ml[u][0]);
     const float f0 = M == ninf ? 0.f : expf(M - nm);
     L *= f0;
     O *= f0;
     M = nm;
 #pragma unroll
-    for (int u = 0; u < kCombBatch; ++u)
-      if (s0 + kCombGroups * u < S) {
+    for (int u = 0; u < BATCH; ++u)
+      if (s0 + kGroups * u < S) {
         const float f = expf(ml[u][0] - nm);
         L += ml[u][1] * f;
         O += f4{o0[u][0], o0[u][1], o1[u][0], o1[u][1]} * f;
       }
   }
   *(f4 *)(po[grp] + d) = O;
-  if ((t & 31) == 0) {
+  if (t % LPG == 0) {
     pm[grp] = M;
     pl[grp] = L;
   }
   __syncthreads();
-  if (t >= kD) return;
-  float Mx = ninf, Ls = 0.f, Os = 0.f;
+  if (t >= kCols) return;
+  // a lane per group: its weight (0 for a group that had no split)
+  const int lane = t & 63;
+  const float m = lane < kGroups ? pm[lane] : ninf;
+  float Mx = m;
 #pragma unroll
-  for (int k = 0; k < kCombGroups; ++k) Mx = fmaxf(Mx, pm[k]);
+  for (int o = 1; o < kGroups; o *= 2) Mx = fmaxf(Mx, __shfl_xor(Mx, o));
+  const float w = m == ninf ? 0.f : expf(m - Mx);
+  float Ls = 0.f, Os = 0.f;
 #pragma unroll
-  for (int k = 0; k < kCombGroups; ++k) {
-    if (k >= S) continue;                                  // a group that had no split
-    const float f = expf(pm[k] - Mx);
+  for (int k = 0; k < kGroups; ++k) {
+    const float f = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), k));
     Ls += pl[k] * f;
     Os += po[k][t] * f;
   }
-  a.o[((int64_t)b * a.Hq + h) * kD + t] = Os / Ls;
+  a.o[((int64_t)b * a.Hq + h) * kD + c0 + t] = Os / Ls;
 }
 
 template <int N3, int N4, int N6, int N8>
@@ -722,8 +729,20 @@ hipError_t launch_attn_decode(const AttnArgs &a, hipStream_t s) {
   if (!dispatch<500>(125 * n3 + 25 * n4 + 5 * a.n6 + a.n8, a, s)) return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_combine_kernel, dim3((unsigned)a.Hq, (unsigned)a.B), dim3(kCombThreads),
-                     0, s, a);
+  // The splits in one memory latency, with few loads per lane for few splits;
+  // many splits come with few heads, whose columns go to several workgroups.
+  // Main kernel and merge, us, over caches not yet read (<32, 8> alone served
+  // all before): 16 x 4096 tokens, 64 heads (4 splits) <32, 2> 31.8, <16, 4>
+  // 32.3, <32, 8> 32.6; 1 x 1777, 64 heads (28) 10.5, 9.9, 10.2; 1 x 4096, 64
+  // heads (64) 13.3, 11.3, 11.5, <8, 8> 11.8; 2 x 9000, 5 heads (141) <16, 4>
+  // 11.9, <8, 8> 11.1, <32, 8> 13.1; 1 x 32768, one head (512) 16.1, 12.3, 19.5.
+  auto merge = [&](auto fn, int parts) {
+    hipLaunchKernelGGL(fn, dim3((unsigned)a.Hq, (unsigned)a.B, (unsigned)parts),
+                       dim3(kCombThreads), 0, s, a);
+  };
+  if (a.splits <= 16) merge(attn_combine_kernel<32, 2>, 1);
+  else if (a.splits <= 64) merge(attn_combine_kernel<16, 4>, 2);
+  else merge(attn_combine_kernel<8, 8>, 4);
   return hipGetLastError();
 }
 

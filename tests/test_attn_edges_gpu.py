@@ -156,3 +156,14 @@ def test_attention_scores_of_minus_infinity(low):
         assert np.isnan(o[0, 1]).all()
         o[0, 1] = ref[0, 1] = 0.0
         assert np.abs(o - ref).max() <= 1e-5 * np.abs(vd).max()
+
+
+@pytest.mark.parametrize("T", [1024, 1025, 4096, 4097, 16385, 32700])
+def test_attention_merge_of_splits(T):
+    """Splits of 64 tokens on both sides of the merge's sizes (16, 64, 256 splits)."""
+    say("attn-splits", T)
+    g = np.random.Generator(np.random.PCG64(T))
+    B, G, Hkv, D = 1, 2, 1, 128
+    q, k, v = (g.normal(size=(B, n, Hkv * h, D)) for n, h in ((1, G), (T, 1), (T, 1)))
+    o, ref, vd = _run(mxq.Format(D, [4, 4, 6, 8]), q[:, 0], k, v, B, G * Hkv, Hkv, T, 0.2)
+    assert np.abs(o - ref).max() <= 1e-5 * np.abs(vd).max()
