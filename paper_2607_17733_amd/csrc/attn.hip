@@ -346,20 +346,14 @@ void attn_decode_kernel(AttnArgs a) {
   const int head = DUP ? n & 7 : n;                        // of lane column n
   const bool lower = !DUP || n < 8;
   const float ninf = -__builtin_inff();
-  // The KV heads of a (sequence, split) share cache lines: they run on one
-  // XCD (workgroups id, id + 8, ... of a round-robin dispatch) where the
-  // (sequence, split) pairs divide evenly.
-  const int Hkv = (int)a.Hkv;
-  const int id = blockIdx.x, units = (int)(gridDim.x / (unsigned)Hkv);
-  int kvh, unit;
-  if ((units & 7) == 0) {
-    const int i = id >> 3;
-    kvh = i % Hkv;
-    unit = i / Hkv * 8 + (id & 7);
-  } else {
-    unit = id / Hkv;
-    kvh = id - unit * Hkv;
-  }
+  // The KV heads of a (sequence, split) share cache lines: they run on one XCD
+  // (XCD x has the workgroups x, x + 8, ... of the dispatch, and takes a
+  // contiguous range of the (sequence, split, head) list).
+  const uint32_t Hkv = (uint32_t)a.Hkv, total = gridDim.x * gridDim.y;
+  const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
+  const uint32_t x = id & 7, per = total >> 3, extra = total & 7;
+  const uint32_t pos = x * per + min(x, extra) + (id >> 3);
+  const int unit = (int)(pos / Hkv), kvh = (int)(pos - (uint32_t)unit * Hkv);
   const int b = unit / a.splits, split = unit - b * a.splits;
   uint8_t *vs = pool + wave * kStage;
 
@@ -690,8 +684,9 @@ void launch_t(const AttnArgs &a, hipStream_t s) {
   const int64_t w = std::min<int64_t>((a.tokens_per_split + kChunk - 1) / kChunk, kWaves);
   const auto fn = a.G <= kMaxG / 2 ? attn_decode_kernel<N3, N4, N6, N8, true>
                                    : attn_decode_kernel<N3, N4, N6, N8, false>;
-  hipLaunchKernelGGL(fn, dim3((unsigned)(a.splits * a.Hkv * a.B)), dim3((unsigned)(64 * w)), 0, s,
-                     a);
+  // (a dispatch holds fewer than 2^32 threads per dimension)
+  hipLaunchKernelGGL(fn, dim3((unsigned)(a.splits * a.Hkv), (unsigned)a.B),
+                     dim3((unsigned)(64 * w)), 0, s, a);
 }
 
 // The kernel for a row's width mix, code = 125 n3 + 25 n4 + 5 n6 + n8 (the

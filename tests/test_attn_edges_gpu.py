@@ -167,3 +167,26 @@ def test_attention_merge_of_splits(T):
     q, k, v = (g.normal(size=(B, n, Hkv * h, D)) for n, h in ((1, G), (T, 1), (T, 1)))
     o, ref, vd = _run(mxq.Format(D, [4, 4, 6, 8]), q[:, 0], k, v, B, G * Hkv, Hkv, T, 0.2)
     assert np.abs(o - ref).max() <= 1e-5 * np.abs(vd).max()
+
+
+def test_attention_more_threads_than_one_grid_dimension():
+    """68 million heads of one token: a wave each, more than 2^32 threads.  Every
+    head returns its own V row, 2^(E - 129) throughout."""
+    B, Hkv, T, D = 65535, 1040, 1, 128
+    rows = B * Hkv
+    assert rows * 64 > 1 << 32
+    if torch.cuda.mem_get_info()[0] < 120 << 30:
+        pytest.skip("needs 100 GB of device memory")
+    say("attn-grid", rows)
+    fmt = mxq.Format(D, [4] * 4)
+    dev = torch.device("cuda")
+    q = torch.zeros((B, Hkv, D), dtype=torch.bfloat16, device=dev)
+    mant = torch.full((rows, fmt.act_packed_bytes()), 0x11, dtype=torch.uint8, device=dev)
+    E = (torch.arange(rows, dtype=torch.int32, device=dev) % 50 + 100).to(torch.uint8)
+    exps = E[:, None].expand(rows, fmt.exp_row_bytes()).contiguous()
+    o = mxq.attn_decode(q, (mant, exps), (mant, exps), fmt, B, Hkv, Hkv, T, 0.1).view(rows, D)
+    for r in range(0, rows, 1 << 22):
+        want = torch.exp2(E[r:r + (1 << 22)].float() - 129)
+        assert bool((o[r:r + (1 << 22)] == want[:, None]).all()), r
+    del o, q, mant, exps
+    torch.cuda.empty_cache()
