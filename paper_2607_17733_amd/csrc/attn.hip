@@ -357,16 +357,17 @@ void attn_decode_kernel(AttnArgs a) {
   const int b = unit / a.splits, split = unit - b * a.splits;
   uint8_t *vs = pool + wave * kStage;
 
-  // the score product's Q operand: head n of the group, the elements of
-  // product j in slot order
+  // the score product's Q operand: head n of the group (columns past the last
+  // head repeat it), the elements of product j in slot order.  No branch, so
+  // that the first rows are loaded before Q arrives: 1 x 4096 tokens, 64 heads
+  // 11.15 -> 10.8 us.
+  const uint32_t sign = a.scale < 0.f ? 0x80008000u : 0u;
   bf8 qop[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    u4 x = {0u, 0u, 0u, 0u};
     const int e0 = Gm::kUniform ? 32 * g + 8 * j : 32 * j + 8 * g;
-    if (head < G)
-      x = *(const u4 *)(a.q + ((int64_t)b * a.Hq + (int64_t)kvh * G + head) * kD + e0);
-    if (a.scale < 0.f) x ^= u4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
+    u4 x = *(const u4 *)(a.q + ((int64_t)b * a.Hq + (int64_t)kvh * G + min(head, G - 1)) * kD + e0);
+    x ^= u4{sign, sign, sign, sign};
     const bf8 y = __builtin_bit_cast(bf8, x);
 #pragma unroll
     for (int i = 0; i < 8; ++i) qop[j][i] = y[slot_elem(Gm::width(j), i)];
@@ -563,7 +564,7 @@ void attn_decode_kernel(AttnArgs a) {
     for (int v = 0; v < kWaves; ++v)
       if (v < nw) M = fmaxf(M, fmaxf(mm[v][c], mm[v][c ^ (kMaxG - kStride)]));
     // without a score above -inf: nothing (or a NaN, which stays)
-    mf[w][c] = mm[w][c] == ninf ? ml[w][c] : expf(mm[w][c] - M);
+    mf[w][c] = mm[w][c] == ninf ? ml[w][c] : exp_f(mm[w][c] - M);
   }
   __syncthreads();
   float *mo = (float *)pool;                               // [kWaves][kMaxG][kD]
