@@ -19,6 +19,8 @@
 // the column in the permutation: the 4-bit columns first, then the 6-bit and
 // the 8-bit ones, each in sorted order.
 #include "mxq_internal.h"
+#include <algorithm>
+#include <type_traits>
 
 namespace mxq {
 
@@ -52,8 +54,9 @@ __device__ inline int64_t sample_ld(const SampleBatch &b, int) { return b.lead; 
 // A lane per column, COLS columns per workgroup (blockIdx.x) and sample
 // (blockIdx.y): the column sums of the sample in row order, to its row of
 // `out` (or added to it).  A wave keeps the next BATCH rows in flight while it
-// sums the current ones.  The kernel is bound by the HBM read once enough rows
-// are in flight: few waves need 32 each (64 loads, the most a wave can count),
+// sums the current ones; the rows left over are one more such set (2047 x 4096:
+// 41.9 us, read one after the other 51.3).  The kernel is bound by the HBM read
+// once enough rows are in flight: few waves need 32 each (64 loads, the most a wave can count),
 // and one wave per workgroup to spread over the CUs; more than 8 per CU do with
 // 4 each, and workgroups of 256 adjacent columns read longer runs.  Sixteen
 // samples of 2048 x 4096 (268 MB): 43.5 us (6.2 TB/s; a launch per sample, whose
@@ -80,7 +83,6 @@ __global__ __launch_bounds__(COLS) void colsq_kernel(Samples sm, int64_t K, doub
       sum += d * d;
     }
   };
-  int64_t r = 0;
   const int64_t nb = rows / BATCH;
   if (nb > 0) {
     uint16_t a[BATCH], b[BATCH];
@@ -99,12 +101,28 @@ __global__ __launch_bounds__(COLS) void colsq_kernel(Samples sm, int64_t K, doub
     } else {
       add(a);
     }
-    r = nb * BATCH;
   }
-  for (; r < rows; ++r) {
-    const double d = bf16_to_f64(p[r * ld]);
-    sum += d * d;
-  }
+  // the rows left over, their loads in flight together too: those of the 1, 8 or
+  // BATCH loads that lie past the end repeat the last row and add 0 (exact: the
+  // sum is never -0)
+  const int rem = (int)(rows - nb * BATCH);
+  auto left = [&](auto n) __attribute__((always_inline)) {
+    constexpr int N = decltype(n)::value;
+    uint16_t v[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] = p[(nb * BATCH + min(u, rem - 1)) * ld];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const double d = u < rem ? bf16_to_f64(v[u]) : 0.0;
+      sum += d * d;
+    }
+  };
+  if (rem > 8)
+    left(std::integral_constant<int, BATCH>{});
+  else if (rem > 1)
+    left(std::integral_constant<int, (BATCH < 8 ? BATCH : 8)>{});
+  else if (rem == 1)
+    left(std::integral_constant<int, 1>{});
   double *o = out + (int64_t)y * K + k;
   *o = accumulate ? *o + sum : sum;
 }
@@ -190,14 +208,18 @@ __global__ __launch_bounds__(kCalThreads) void rank_perm_kernel(const double *__
   perm[pos] = (int32_t)i;
 }
 
+// max_rows: the rows of the longest sample.  Below 64 rows a wave has no whole
+// pair of batches to overlap, and 64 columns per workgroup only make more
+// workgroups (sixteen samples of 31 x 4096: 9.3 us, wide ones 6.7; of 100 x 4096
+// 12.6 and 12.6, of 300 18.4 and 29.7).
 template <class Samples>
-hipError_t go_colsq(const Samples &sm, int64_t n, int64_t K, double *out, bool accumulate,
-                    hipStream_t stream) {
+hipError_t go_colsq(const Samples &sm, int64_t n, int64_t max_rows, int64_t K, double *out,
+                    bool accumulate, hipStream_t stream) {
   auto launch = [&](auto fn, int cols) {
     hipLaunchKernelGGL(fn, dim3((unsigned)((K + cols - 1) / cols), (unsigned)n), dim3(cols), 0,
                        stream, sm, K, out, accumulate ? 1 : 0);
   };
-  if ((K + 63) / 64 * n <= 8 * (int64_t)device_cu_count())
+  if (max_rows >= 64 && (K + 63) / 64 * n <= 8 * (int64_t)device_cu_count())
     launch(colsq_kernel<Samples, 64, 32>, 64);
   else
     launch(colsq_kernel<Samples, 256, 4>, 256);
@@ -216,13 +238,14 @@ hipError_t go_add(const double *part, int64_t n, int64_t K, double *s, bool accu
 
 hipError_t launch_calib_colsq(const uint16_t *x, int64_t rows, int64_t ld, int64_t K, double *s,
                               bool accumulate, hipStream_t stream) {
-  return go_colsq(SampleBatch{x, 0, rows, ld}, 1, K, s, accumulate, stream);
+  return go_colsq(SampleBatch{x, 0, rows, ld}, 1, rows, K, s, accumulate, stream);
 }
 
 hipError_t launch_calib_colsq_samples(const uint16_t *x, int64_t n, int64_t rows, int64_t ld,
                                       int64_t sample_stride, int64_t K, double *part, double *s,
                                       bool accumulate, hipStream_t stream) {
-  const hipError_t e = go_colsq(SampleBatch{x, sample_stride, rows, ld}, n, K, part, false, stream);
+  const hipError_t e = go_colsq(SampleBatch{x, sample_stride, rows, ld}, n, rows, K, part,
+                                false, stream);
   return e != hipSuccess ? e : go_add(part, n, K, s, accumulate, stream);
 }
 
@@ -230,12 +253,14 @@ hipError_t launch_calib_colsq_list(const uint16_t *const *x, const int64_t *rows
                                    const int64_t *ld, int64_t n, int64_t K, double *part,
                                    double *s, bool accumulate, hipStream_t stream) {
   SampleList l{};
+  int64_t max_rows = 0;
   for (int64_t i = 0; i < n; ++i) {
     l.x[i] = x[i];
     l.rows[i] = rows[i];
+    max_rows = std::max(max_rows, rows[i]);
     l.ld[i] = ld[i];
   }
-  const hipError_t e = go_colsq(l, n, K, part, false, stream);
+  const hipError_t e = go_colsq(l, n, max_rows, K, part, false, stream);
   return e != hipSuccess ? e : go_add(part, n, K, s, accumulate, stream);
 }
 

@@ -138,3 +138,16 @@ def test_many_samples_take_wide_workgroups():
         samples = _samples(rows, n, rows, K)
         s = mxq.calib_colsq_samples(torch.stack([to_dev_bf16(b) for b in samples]))
         assert np.array_equal(s.cpu().numpy(), calib.column_sensitivity(samples))
+
+
+@pytest.mark.parametrize("rows", [1, 3, 4, 5, 63, 64, 65, 72, 73, 95, 127])
+def test_left_over_rows(rows):
+    """The rows after a kernel's whole batches (of 4 rows below 64 rows, of 32
+    from there on) are summed in row order, on both sides of the rule."""
+    say("calib-left-over", rows)
+    samples = _samples(rows, 3, rows, 160)
+    samples[1][-1, 7] = 0x7FC0                           # a NaN in the last row
+    s = mxq.calib_colsq_samples(torch.stack([to_dev_bf16(b) for b in samples]))
+    assert np.array_equal(s.cpu().numpy(), calib.column_sensitivity(samples), equal_nan=True)
+    one = mxq.calib_colsq(to_dev_bf16(samples[0]))
+    assert np.array_equal(one.cpu().numpy(), calib.column_sensitivity(samples[:1]))
