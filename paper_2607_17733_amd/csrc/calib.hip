@@ -145,8 +145,11 @@ __device__ inline double sort_key(double v) { return v != v ? __builtin_inf() : 
 // instruction: the rank of K columns is K^2 / 64 compares spread over
 // K / kRankCols workgroups (K = 4096: 8.9 us; one thread per column, sixteen
 // workgroups walking all K keys, took 310 us).
+// PRE sets of 64 columns a wave has in flight: 8 for long rows, no more than
+// there are for short ones (K = 32: 8 sets 5.9 us, 1 set 4.0).
 constexpr int kRankCols = 16;
 
+template <int PRE>
 __global__ __launch_bounds__(kCalThreads) void rank_perm_kernel(const double *__restrict__ s,
                                                                 int64_t K, int64_t n4,
                                                                 int64_t n6, int64_t n8,
@@ -163,18 +166,17 @@ __global__ __launch_bounds__(kCalThreads) void rank_perm_kernel(const double *__
     before[c] = 0;
   }
   // 64 columns from j0: all of them before the workgroup's columns (equal
-  // sensitivities sort first), all after, or mixed.  The loads of eight such
+  // sensitivities sort first), all after, or mixed.  The loads of PRE such
   // sets are issued together: one after the other they were most of the time.
-  constexpr int kPre = 8;
-  for (int64_t jb = 64 * wave; jb < K; jb += kPre * kCalThreads) {
-    double raw[kPre];
+  for (int64_t jb = 64 * wave; jb < K; jb += PRE * kCalThreads) {
+    double raw[PRE];
 #pragma unroll
-    for (int u = 0; u < kPre; ++u) {
+    for (int u = 0; u < PRE; ++u) {
       const int64_t j = jb + u * kCalThreads + lane;
       raw[u] = s[j < K ? j : K - 1];
     }
 #pragma unroll
-    for (int u = 0; u < kPre; ++u) {
+    for (int u = 0; u < PRE; ++u) {
       const int64_t j0 = jb + u * kCalThreads, j = j0 + lane;
       const bool in = j < K;
       const double sj = in ? sort_key(raw[u]) : -__builtin_inf();   // not before any column
@@ -267,7 +269,10 @@ hipError_t launch_calib_colsq_list(const uint16_t *const *x, const int64_t *rows
 hipError_t launch_calib_perm(const double *s, int64_t K, int64_t n6, int64_t n8, int32_t *perm,
                              hipStream_t stream) {
   const int64_t blocks = (K + kRankCols - 1) / kRankCols;
-  hipLaunchKernelGGL(rank_perm_kernel, dim3((unsigned)blocks), dim3(kCalThreads), 0, stream, s,
+  const auto fn = K <= kCalThreads       ? rank_perm_kernel<1>
+                  : K <= 4 * kCalThreads ? rank_perm_kernel<4>
+                                         : rank_perm_kernel<8>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kCalThreads), 0, stream, s,
                      K, K / 32 - n6 - n8, n6, n8, perm);
   return hipGetLastError();
 }

@@ -151,3 +151,16 @@ def test_left_over_rows(rows):
     assert np.array_equal(s.cpu().numpy(), calib.column_sensitivity(samples), equal_nan=True)
     one = mxq.calib_colsq(to_dev_bf16(samples[0]))
     assert np.array_equal(one.cpu().numpy(), calib.column_sensitivity(samples[:1]))
+
+
+@pytest.mark.parametrize("K", [224, 256, 288, 992, 1024, 1056, 2080])
+def test_ranks_of_short_rows(K):
+    """Widths on both sides of the lines between one, four and eight sets of
+    columns in flight, with ties, NaN and both infinities."""
+    say("calib-perm-short", K)
+    g = np.random.Generator(np.random.PCG64(K))
+    s = g.integers(0, K // 8, size=K).astype(np.float64)
+    s[[5, 100]] = np.nan
+    s[7], s[K - 1] = np.inf, -np.inf
+    perm = mxq.calib_perm(torch.from_numpy(s).cuda(), 2, 1)
+    assert np.array_equal(perm.cpu().numpy(), calib.allocate(s, 2, 1)[0])
