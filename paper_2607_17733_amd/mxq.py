@@ -399,12 +399,19 @@ def peak_mfma(kind: str, iters: int, sink):
 # --------------------------------------------------------------------------
 # Calibration (offline): permutation and width map from calibration samples
 
+def _sample(x, dim: int):
+    """A calibration sample (or, 3-D, a batch of them), checked."""
+    if not (isinstance(x, torch.Tensor) and x.is_cuda and x.dtype == torch.bfloat16
+            and x.dim() == dim and x.stride(dim - 1) == 1):
+        raise MxqError("calibration samples must be %d-D bf16 device tensors with unit "
+                       "column stride" % dim)
+    return x
+
+
 def calib_colsq(x, s=None, accumulate: bool = False):
-    """Column sensitivities of one calibration sample x (bf16 [rows, >=K]):
+    """Column sensitivities of one calibration sample x (bf16 [rows, K]):
     s[k] = sum_r x[r, k]^2 in float64 (added to s when accumulate)."""
-    if x.dtype != torch.bfloat16 or x.dim() != 2 or x.stride(1) != 1:
-        raise MxqError("calibration samples must be 2-D bf16 with unit column stride")
-    rows, K = x.shape
+    rows, K = _sample(x, 2).shape
     if s is None:
         if accumulate:
             raise MxqError("accumulate needs the running sensitivities")
@@ -415,11 +422,9 @@ def calib_colsq(x, s=None, accumulate: bool = False):
 
 
 def calib_colsq_samples(x, s=None, accumulate: bool = False, work=None):
-    """Column sensitivities of a batch of samples x (bf16 [n, rows, >=K]),
+    """Column sensitivities of a batch of samples x (bf16 [n, rows, K]),
     summed in sample order (equal to one calib_colsq call per sample)."""
-    if x.dtype != torch.bfloat16 or x.dim() != 3 or x.stride(2) != 1:
-        raise MxqError("calibration samples must be 3-D bf16 with unit column stride")
-    n, rows, K = x.shape
+    n, rows, K = _sample(x, 3).shape
     if s is None:
         if accumulate:
             raise MxqError("accumulate needs the running sensitivities")
@@ -452,8 +457,9 @@ def calib_counts(d_in: int, R: float, s_layer: float, n8_blocks: int = 1):
 
 def calib_perm(s, n6: int, n8: int, perm=None):
     """The permutation of Algorithm 2 (int32 device tensor [K])."""
-    if s.dtype != torch.float64 or s.dim() != 1:
-        raise MxqError("sensitivities must be a 1-D float64 tensor")
+    if not (isinstance(s, torch.Tensor) and s.is_cuda and s.dtype == torch.float64
+            and s.dim() == 1):
+        raise MxqError("sensitivities must be a 1-D float64 device tensor")
     K = s.numel()
     if perm is None:
         perm = torch.empty(K, dtype=torch.int32, device=s.device)
@@ -470,7 +476,7 @@ def _colsq_list(samples):
     CALIB_LIST_MAX samples: one sample's columns fill a fraction of the GPU.
     None for samples that are not all bf16 [rows, K] of one K and device
     (they are summed one call each)."""
-    if len(samples) < 2 or not all(isinstance(x, torch.Tensor) and x.dim() == 2
+    if len(samples) < 2 or not all(isinstance(x, torch.Tensor) and x.is_cuda and x.dim() == 2
                                    and x.dtype == torch.bfloat16 and x.stride(1) == 1
                                    and x.shape[1] == samples[0].shape[1]
                                    and x.device == samples[0].device for x in samples):
@@ -492,7 +498,11 @@ def _colsq_list(samples):
 def calibrate(samples, s_layer: float, R: float, n8_blocks: int = 1):
     """One layer: sensitivities over the samples, the block counts and the
     permutation.  Returns (perm int32 device tensor, widths list)."""
-    s = _colsq_list(samples) if isinstance(samples, (list, tuple)) else None
+    s = None
+    if isinstance(samples, (list, tuple)):
+        for x in samples:
+            _sample(x, 2)
+        s = _colsq_list(samples)
     if s is None:
         for i, x in enumerate(samples):
             s = calib_colsq(x, s, accumulate=i > 0)

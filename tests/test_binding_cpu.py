@@ -14,7 +14,8 @@ from paper_2607_17733_amd import mxq
 LAUNCHING = {"mxq_quantize_act", "mxq_quantize_rows", "mxq_quantize_act_rmsnorm",
              "mxq_quantize_act_swiglu",
              "mxq_pack_weights", "mxq_gemm", "mxq_gemm_partials", "mxq_unpack_act",
-             "mxq_unpack_weights", "mxq_attn_decode"}
+             "mxq_unpack_weights", "mxq_attn_decode", "mxq_calib_colsq",
+             "mxq_calib_colsq_samples", "mxq_calib_colsq_list", "mxq_calib_perm"}
 
 
 class _NoLaunch:
@@ -180,3 +181,19 @@ def test_sizes_follow_the_library():
         fmt.act_bytes(-1)
     with pytest.raises(mxq.MxqError, match="width"):
         mxq.Format(64, [6, 4]).weight_bytes(1)
+
+
+def test_calibration_rejects_host_tensors():
+    """Host samples and sensitivities raise before any launch: a kernel would
+    read host addresses."""
+    real = mxq.lib()
+    with mock.patch.object(mxq, "lib", lambda path=mxq.LIB_PATH: _NoLaunch(real)):
+        x = torch.zeros((4, 64), dtype=torch.bfloat16)
+        s = torch.zeros(64, dtype=torch.float64)
+        for call in (lambda: mxq.calib_colsq(x), lambda: mxq.calib_colsq(x, s, accumulate=True),
+                     lambda: mxq.calib_colsq_samples(x[None]), lambda: mxq.calib_perm(s, 0, 1),
+                     lambda: mxq.calibrate([x, x], 0.5, 0.2),
+                     lambda: mxq.calibrate((x,), 0.5, 0.2),
+                     lambda: mxq.calibrate(iter([x, x]), 0.5, 0.2)):
+            with pytest.raises(mxq.MxqError, match="device tensor"):
+                call()
