@@ -408,14 +408,28 @@ def _sample(x, dim: int):
     return x
 
 
+def _dev_array(t, n: int, dtype, what: str, dev):
+    """A contiguous device array of at least n elements on `dev`."""
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype
+            and t.is_contiguous()):
+        raise MxqError("%s must be a contiguous %s device tensor" % (what, dtype))
+    if t.numel() < n:
+        raise MxqError("%s holds %d elements, %d needed" % (what, t.numel(), n))
+    if t.device != dev:
+        raise MxqError("%s is on %s, not %s" % (what, t.device, dev))
+    return t
+
+
 def calib_colsq(x, s=None, accumulate: bool = False):
     """Column sensitivities of one calibration sample x (bf16 [rows, K]):
-    s[k] = sum_r x[r, k]^2 in float64 (added to s when accumulate)."""
+    s[k] = sum_r x[r, k]^2 in float64 (added to s when accumulate).  s holds
+    at least K columns; those past K stay as they are."""
     rows, K = _sample(x, 2).shape
     if s is None:
         if accumulate:
             raise MxqError("accumulate needs the running sensitivities")
         s = torch.empty(K, dtype=torch.float64, device=x.device)
+    _dev_array(s, K, torch.float64, "sensitivities", x.device)
     _check(lib().mxq_calib_colsq(_ptr(x), rows, x.stride(0), K, _ptr(s),
                                  1 if accumulate else 0, _stream()), "mxq_calib_colsq")
     return s
@@ -431,6 +445,8 @@ def calib_colsq_samples(x, s=None, accumulate: bool = False, work=None):
         s = torch.empty(K, dtype=torch.float64, device=x.device)
     if work is None:
         work = torch.empty(n * K, dtype=torch.float64, device=x.device)
+    _dev_array(s, K, torch.float64, "sensitivities", x.device)
+    _dev_array(work, n * K, torch.float64, "work", x.device)
     _check(lib().mxq_calib_colsq_samples(_ptr(x), n, rows, x.stride(1), x.stride(0), K,
                                          _ptr(work), _ptr(s), 1 if accumulate else 0,
                                          _stream()), "mxq_calib_colsq_samples")
@@ -458,11 +474,12 @@ def calib_counts(d_in: int, R: float, s_layer: float, n8_blocks: int = 1):
 def calib_perm(s, n6: int, n8: int, perm=None):
     """The permutation of Algorithm 2 (int32 device tensor [K])."""
     if not (isinstance(s, torch.Tensor) and s.is_cuda and s.dtype == torch.float64
-            and s.dim() == 1):
-        raise MxqError("sensitivities must be a 1-D float64 device tensor")
+            and s.dim() == 1 and s.is_contiguous()):
+        raise MxqError("sensitivities must be a contiguous 1-D float64 device tensor")
     K = s.numel()
     if perm is None:
         perm = torch.empty(K, dtype=torch.int32, device=s.device)
+    _dev_array(perm, K, torch.int32, "perm", s.device)
     _check(lib().mxq_calib_perm(_ptr(s), K, int(n6), int(n8), _ptr(perm), _stream()),
            "mxq_calib_perm")
     return perm
@@ -497,11 +514,14 @@ def _colsq_list(samples):
 
 def calibrate(samples, s_layer: float, R: float, n8_blocks: int = 1):
     """One layer: sensitivities over the samples, the block counts and the
-    permutation.  Returns (perm int32 device tensor, widths list)."""
+    permutation.  Returns (perm int32 device tensor, widths list).  The first
+    sample's width is the layer's: no later one may be wider (a narrower one
+    counts for the columns that it has)."""
     s = None
     if isinstance(samples, (list, tuple)):
         for x in samples:
-            _sample(x, 2)
+            if _sample(x, 2).shape[1] > samples[0].shape[1]:
+                raise MxqError("a calibration sample is wider than the first one")
         s = _colsq_list(samples)
     if s is None:
         for i, x in enumerate(samples):

@@ -197,3 +197,29 @@ def test_calibration_rejects_host_tensors():
                      lambda: mxq.calibrate(iter([x, x]), 0.5, 0.2)):
             with pytest.raises(mxq.MxqError, match="device tensor"):
                 call()
+
+
+def test_calibration_rejects_short_or_wrong_outputs(host_as_device):
+    """Sensitivities, scratch and permutations that a kernel would write past
+    the end of raise before any launch, as do samples that widen."""
+    x = torch.zeros((2, 4, 96), dtype=torch.bfloat16)
+    f64 = lambda n: torch.zeros(n, dtype=torch.float64)
+    for s in (f64(95), f64(192)[::2], torch.zeros(96), torch.zeros(96, dtype=torch.int64)):
+        with pytest.raises(mxq.MxqError, match="sensitivities"):
+            mxq.calib_colsq(x[0], s)
+        with pytest.raises(mxq.MxqError, match="sensitivities"):
+            mxq.calib_colsq(x[0], s, accumulate=True)
+        with pytest.raises(mxq.MxqError, match="sensitivities"):
+            mxq.calib_colsq_samples(x, s, work=f64(192))
+    for work in (f64(191), torch.zeros(192)):
+        with pytest.raises(mxq.MxqError, match="work"):
+            mxq.calib_colsq_samples(x, work=work)
+    for perm in (torch.zeros(95, dtype=torch.int32), torch.zeros(96, dtype=torch.int64)):
+        with pytest.raises(mxq.MxqError, match="perm"):
+            mxq.calib_perm(f64(96), 0, 1, perm=perm)
+    with pytest.raises(mxq.MxqError, match="sensitivities"):
+        mxq.calib_perm(f64(192)[::2], 0, 1)
+    with pytest.raises(mxq.MxqError, match="wider"):
+        mxq.calibrate([x[0, :, :64], x[0]], 0.5, 0.2)
+    with pytest.raises(mxq.MxqError, match="wider"):
+        mxq.calibrate([x[0, :, :64], x[0, :, :32], x[0]], 0.5, 0.2)
