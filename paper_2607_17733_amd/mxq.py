@@ -7,6 +7,7 @@ is no fallback: if the library is missing the calls raise ``MxqError``.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 
 import numpy as np
@@ -141,6 +142,13 @@ class Format:
     def ref(self):
         return self._ref
 
+    def _size_of(self, count: int, tile: int, unit: int, what: str) -> int:
+        """Bytes of `count` rows or columns in whole tiles of `tile`."""
+        n = operator.index(count)
+        if n < 0:
+            _check(2, what)
+        return (n + tile - 1) // tile * self._units()[unit]
+
     def _units(self):
         """What every size is a multiple of: the bytes of a 16-row activation
         tile and its scales, a 128-column weight super-slab and its scales, a
@@ -173,25 +181,17 @@ class Format:
 
     def act_bytes(self, M: int) -> int:
         """The activation operand image of M rows (mxq_quantize_act)."""
-        if M < 0:
-            _check(2, "mxq_act_bytes")
-        return (M + 15) // 16 * self._units()[0]
+        return self._size_of(M, 16, 0, "mxq_act_bytes")
 
     def act_exp_bytes(self, M: int) -> int:
         """Its scale bytes."""
-        if M < 0:
-            _check(2, "mxq_act_exp_bytes")
-        return (M + 15) // 16 * self._units()[1]
+        return self._size_of(M, 16, 1, "mxq_act_exp_bytes")
 
     def weight_bytes(self, N: int) -> int:
-        if N < 0:
-            _check(2, "mxq_weight_bytes")
-        return (N + 127) // 128 * self._units()[2]
+        return self._size_of(N, 128, 2, "mxq_weight_bytes")
 
     def weight_exp_bytes(self, N: int) -> int:
-        if N < 0:
-            _check(2, "mxq_weight_exp_bytes")
-        return (N + 127) // 128 * self._units()[3]
+        return self._size_of(N, 128, 3, "mxq_weight_exp_bytes")
 
 
 def _bf16_2d(t, K, what):

@@ -181,6 +181,10 @@ def test_sizes_follow_the_library():
         fmt.act_bytes(-1)
     with pytest.raises(mxq.MxqError, match="width"):
         mxq.Format(64, [6, 4]).weight_bytes(1)
+    for size in (fmt.act_bytes, fmt.act_exp_bytes, fmt.weight_bytes, fmt.weight_exp_bytes):
+        assert size(np.int64(40)) == size(40)
+        with pytest.raises(TypeError):
+            size(2.5)
 
 
 def test_calibration_rejects_host_tensors():
