@@ -21,7 +21,7 @@
 // step is read once for all of the launch's 16-row activation tiles (up to
 // four: M <= 64).  A workgroup
 // owns a unit of four 16-column slabs, or two where four would leave CUs
-// without a workgroup, or (M <= 16) one unit of 5 or 6 consecutive slabs
+// without a workgroup, or (M <= 16) one unit of 5 to 7 consecutive slabs
 // per CU where that balances the CUs (one activation load feeds all of
 // them); its nw waves
 // (2 to 8, the most at which every unit is resident by the kernel's register
@@ -98,7 +98,7 @@ __device__ inline uint32_t lo_codes(uint32_t w) {
 // T: 16-row activation tiles (M <= 16 T); SL: 16-column slabs per
 // workgroup (one activation load feeds all of them).  A unit is SL
 // consecutive slabs; with 2 or 4 it lies inside one 128-column super-slab,
-// with 5 or 6 (one unit per CU where that balances the CUs) it may cross
+// with 5 to 7 (one unit per CU where that balances the CUs) it may cross
 // into the next super-slab.
 template <bool FULL, int T, int SL>
 __global__ __launch_bounds__(64 * kMaxWaves) void gemm_decode_kernel(GemmArgs g) {
@@ -392,7 +392,7 @@ hipError_t launch_gemm_decode(const GemmArgs &a, hipStream_t stream) {
   const int cus = device_cu_count();
   // four slabs per workgroup (half the activation loads per weight byte)
   // when that still gives every CU a workgroup, else two; where the slabs
-  // come to 5 or 6 per CU (M <= 16), one unit of that many per CU, since four-slab
+  // come to 5 to 7 per CU (M <= 16), one unit of that many per CU, since four-slab
   // units would give some CUs one unit and others two (the kernel takes as
   // long as its busiest CUs: 448 four-slab units on 256 CUs ran 26.1 us,
   // 512 ran 27.5 us)
@@ -408,10 +408,11 @@ hipError_t launch_gemm_decode(const GemmArgs &a, hipStream_t stream) {
       const dim3 grid((unsigned)units), block((unsigned)(64 * decode_waves<FULL, T, SL>(units, cus)));
       hipLaunchKernelGGL((gemm_decode_kernel<FULL, T, SL>), grid, block, 0, stream, a);
     };
-    // (one activation tile only: with more, units of 5 or 6 slabs spill)
-    if (T == 1 && spc >= 5 && spc <= 6) {
+    // (one activation tile only: with more, units of 5 to 7 slabs spill)
+    if (T == 1 && spc >= 5 && spc <= 7) {
       if constexpr (T == 1) {
-        if (spc == 6) one_per_cu(std::integral_constant<int, 6>{});
+        if (spc == 7) one_per_cu(std::integral_constant<int, 7>{});
+        else if (spc == 6) one_per_cu(std::integral_constant<int, 6>{});
         else one_per_cu(std::integral_constant<int, 5>{});
       }
     } else if (quad) {

@@ -53,6 +53,7 @@
 #include "mxq_device.h"
 #include "mxq_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace mxq {
@@ -930,20 +931,67 @@ hipError_t go_split(const GemmArgs &a, hipStream_t stream) {
 //     (29.0, 28.4); 300 x 8192 x 8192 33.9, 41.5 (47, 51)
 //   more workgroups than that: the tiled kernel (2048 x 4096 x 4096 41.6, two
 //     shares 49.7).
-// Up to 64 rows the streaming kernel keeps the shapes where its deeper
-// pipeline counts: at most 16 rows and column tiles for fewer than 3/4 of the
-// CUs (16 x 4096 x 14336 over new weights 11.7, split 12.9) or more than all, at
-// most 32 rows and 64 column tiles (24 x 8192 x 8192 15.1, 21.5), and long K (64
-// x 28672 x 8192 56, 62).  One row tile over weights of more than 64 MB reads
-// them past the caches: 16 x 8192 x 28672 over new weights 25.3 (28.0 through
-// the caches, 28.0 the streaming kernel).
+// Up to 64 rows the streaming kernel is the other choice; split_small draws the
+// line.  One row tile over weights of more than 64 MB reads them past the
+// caches: 16 x 8192 x 28672 over new weights 25.3 (28.0 through the caches, 28.0
+// the streaming kernel).
 enum Split { kNoSplit, kSplit4x32, kSplit4x32Once, kSplit4x64, kSplit2x64 };
+
+// Whether M <= 64 rows over nt column tiles take a split of K.  Times of the
+// streaming kernel, split, in us over new weights; 468 and 368 are maps of 10 %
+// 6- and 8-bit blocks, 468' of 10 % and 5 %.
+bool split_small(const GemmArgs &a, const LGeo &lg, int64_t nt, int64_t cus) {
+  const int steps = lg.nsteps;
+  int segs = 0;
+#pragma unroll
+  for (int s = 0; s < kSegs; ++s) segs += lg.S[s] > 0;
+  // At most 16 rows: the streaming kernel's two- and four-slab units and, from
+  // 4/8 to 7/8 column tiles per CU, its units of 5 to 7 slabs keep the CUs
+  // evenly loaded.  Split wins past 3/4 over long K, up to 7/8 where there are
+  // 8-bit and no 3-bit steps: 16 x 8192 x 28672 468' 26.7, 24.8, 368 22.3, 22.5,
+  // all 6-bit 37.9, 39.0; 16 x 4096 x 28672 all 4-bit 13.1, 14.0; 16 x 2048 x
+  // 28672 468' 10.3, 10.6; 16 x 6144 x 30720 468' 21.2, 19.5; 16 x 8192 x 24576
+  // 468' 23.8, 24.6, all 6-bit 33.3, 37.5.  Mixed full-clamp maps from 36 steps up:
+  // 16 x 4096 x 28672 468' 20.5, 19.1, 368 18.8, 15.4; all 6-bit 22.8, 23.0.
+  if (a.M <= 16) {
+    if (4 * nt <= 3 * cus || nt > cus) return false;
+    if (a.full && segs > 1 && lg.S[3] > 0) return steps >= 36;
+    return steps >= 44 && (8 * nt > 7 * cus || (lg.S[3] > 0 && lg.S[0] == 0));
+  }
+  // (its pipeline is the deeper one: 64 x 28672 x 8192 468 56.0, 60.4)
+  if (steps > 160) return false;
+  // More column tiles than CUs leave split its 64-row tiles: short K does not
+  // fill them (24 x 1024 x 33000 468' 11.3, 12.5; 24 x 8192 x 33000 51.1, 45.0).
+  if (nt > cus) return steps >= (a.M <= 32 ? 48 : 10);
+  // More two-slab units than CUs: some CUs have two (24 x 4096 x 10240 468'
+  // 16.9, 13.4; 40 x 8192 x 14336 37, 21).  Two column tiles per four CUs are one
+  // four-slab unit each, even again (24 x 4096 x 16384 all 4-bit 10.7, 13.7, 468'
+  // 16.2, 15.9).
+  if (4 * nt > cus) return a.M > 32 || 2 * nt != cus;
+  // One unit per CU.  A step takes the streaming kernel less time than split (0.15
+  // and 0.2 us), a row tile and a change of segment more: 24 x 4096 x 4096 468
+  // 10.4, 12.2; 40 x 4096 x 4096 13.1, 11.5, all 4-bit 8.9, 9.9; 40 x 8192 x 4096
+  // 468 18.4, 18.8, all 6-bit 25.4, 31.8; 64 x 8192 x 4096 468 21.6, 19.7, all
+  // 4-bit 15.5, 16.6; 64 x 14336 x 4096 368 28.8, 32.3.  Few column tiles share
+  // their activations over fewer CUs, so split reaches further: 40 x 8192 x 1024
+  // 468 17.7, 13.6; 40 x 10240 x 1024 468' 18.0, 14.9, all 6-bit 30.0, 37.5.
+  if (a.M <= 32) return false;
+  const bool t4 = a.M > 48;
+  const bool few = 16 * nt <= cus;
+  int most = std::max((t4 ? 53 : 21) + 13 * segs, few ? 100 : 0);
+  // Full clamp: the split kernel restores an operand at a time in its 6-bit steps
+  // (40 x 3072 x 4096 468' 11.6, 12.9; 64 x 8192 x 4096 468 22.9, 24.7, 368 23.7,
+  // 19.9, all 6-bit (64 x 6144 x 4096) 28.4, 25.3; 40 x 8192 x 1024 468 19.0, 21.9,
+  // 368 19.7, 15.4).
+  if (a.full)
+    most = segs == 1 || lg.S[0] > 0 ? (t4 ? 160 : few ? 100 : 60) : (t4 || few ? 60 : 33);
+  return steps + nt / 4 <= most;
+}
+
 Split split_for(const GemmArgs &a, int cus) {
   const LGeo lg(a.n3, a.n4, a.n6, a.n8);
   const int64_t nt = (a.N + BN - 1) / BN, u1 = (a.M + 31) / 32 * nt, u2 = (a.M + 63) / 64 * nt;
-  if (a.M <= 16 && (4 * nt < 3 * cus || nt > cus)) return kNoSplit;
-  if (a.M > 16 && a.M <= MXQ_DECODE_MAX_M && (lg.nsteps > 160 || (a.M <= 32 && nt <= 64)))
-    return kNoSplit;
+  if (a.M <= MXQ_DECODE_MAX_M && !split_small(a, lg, nt, cus)) return kNoSplit;
   if (u1 <= cus) return a.M <= 32 && nt * a.w_super > (64 << 20) ? kSplit4x32Once : kSplit4x32;
   return u2 <= cus ? kSplit4x64 : u2 <= 2 * cus ? kSplit2x64 : kNoSplit;
 }

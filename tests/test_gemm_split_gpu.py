@@ -56,3 +56,43 @@ def test_split_gemm_reads_large_weights_once():
                        case.widths)
     check_gemm(out["y"].cpu().numpy()[:, cols], Yref, qa, ea, qw[cols], ew[cols], case.widths,
                case.name)
+
+
+@pytest.mark.parametrize("M,K,N,counts,clamp", [
+    # at most 16 rows: 43 and 44 steps of 8-bit blocks over 225 column tiles; 3-bit
+    # blocks up to 224 column tiles; a mixed full-clamp map of 35 and 36 steps
+    (16, 2752, 28673, (0, 0, 0, 86), "sym"),
+    (9, 2816, 28673, (0, 0, 0, 88), "sym"),
+    (5, 5216, 28672, (152, 0, 6, 5), "sym"),
+    (16, 2240, 24577, (0, 0, 36, 34), "full"),
+    (3, 2304, 24577, (0, 0, 36, 36), "full"),
+    # two column tiles per four CUs; more column tiles than CUs, 9 and 10 steps
+    (24, 256, 16384, (0, 4, 2, 2), "sym"),
+    (40, 576, 32800, (0, 0, 10, 8), "sym"),
+    (40, 640, 32800, (0, 0, 10, 10), "sym"),
+    # 33 to 64 rows: up to 16 column tiles, and the lines of one and two segments
+    (48, 6272, 1000, (0, 0, 0, 196), "sym"),
+    (33, 6336, 1000, (0, 0, 0, 198), "sym"),
+    (40, 3840, 2100, (0, 120, 0, 0), "sym"),
+    (40, 3968, 2100, (0, 124, 0, 0), "sym"),
+    (64, 4768, 2100, (0, 0, 75, 74), "sym"),
+    (50, 4832, 2100, (0, 0, 75, 76), "sym"),
+    # and under the full clamp: mixed maps with and without 3-bit blocks
+    (40, 1824, 2100, (0, 0, 29, 28), "full"),
+    (40, 1888, 2100, (0, 0, 30, 29), "full"),
+    (64, 4480, 2100, (70, 0, 35, 35), "full"),
+])
+def test_up_to_64_rows_on_both_sides(M, K, N, counts, clamp):
+    """Shapes of up to 64 rows on both sides of the lines between the streaming
+    kernel and split (256 CUs), over a part of the columns where there are many."""
+    say("gemm-split-small", M, K, N, counts, clamp)
+    n3, n4, n6, n8 = counts
+    assert K == 32 * sum(counts)
+    case = W.random_case(M * 13 + N, M, K, N, (n3 + n4, n6, n8), perm="scales")
+    case.widths[:n3] = [3] * n3 if isinstance(case.widths, list) else 3
+    out = gpu_run(case, fmt_for(case, "rne", clamp))
+    qa, ea, qw, ew = oracle_quant(case, "rne", clamp)
+    cols = np.r_[0:150, N // 2:N // 2 + 150, N - 150:N]
+    qc, ec = np.ascontiguousarray(qw[cols]), np.ascontiguousarray(ew[cols])
+    check_gemm(out["y"].cpu().numpy()[:, cols], oracle.gemm(qa, ea, qc, ec, case.widths), qa, ea,
+               qc, ec, case.widths, case.name)
