@@ -92,3 +92,22 @@ def test_weight_rows_at_the_staging_limit(K, clamp):
     qw, ew = oracle.quantize(case.w_bits, perm=case.perm, widths=case.widths,
                              clamp_mode=1 if clamp == "full" else 0)
     check_pack_w(case, {"w_mant": wm, "w_exp": we}, qw, ew, fmt)
+
+
+@pytest.mark.parametrize("M,K,widths", [(4201, 2048, "468"), (530, 14336, "468"),
+                                        (300, 40960, "8")])
+def test_silu_groups_of_one_workgroup(M, K, widths):
+    """More row groups than workgroups, and no multiple of them: a workgroup's
+    groups lie a grid apart; rows past the input are zeros."""
+    say("silu-groups", M, K, widths)
+    nb = K // 32
+    w = [8] * nb if widths == "8" else [4] * (nb - 20) + [6] * 10 + [8] * 10
+    case = W.random_case(M + K, M, K, 16, (0, 0, nb) if widths == "8" else (nb - 20, 10, 10),
+                         perm="random")
+    g = np.random.Generator(np.random.PCG64(M))
+    up = fused.f32_to_bf16(g.normal(size=(M, K)).astype(np.float32))
+    fmt = fmt_for(case)
+    am, ae = mxq.quantize_act_swiglu(to_dev_bf16(case.a_bits), to_dev_bf16(up), fmt)
+    qa, ea = oracle.quantize(fused.swiglu_bf16(case.a_bits, up), perm=case.perm, widths=w)
+    q, E, pad_ok = decode_act(am.cpu().numpy(), ae.cpu().numpy(), w, M)
+    assert np.array_equal(q, qa) and np.array_equal(E, ea) and pad_ok
