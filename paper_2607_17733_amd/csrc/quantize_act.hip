@@ -880,6 +880,14 @@ static RowGroups row_groups(const QuantArgs &a, int cus) {
   // (K = 14336, M = 4096: 4 rows and 1024 threads, one per CU, 82 us, 2 rows
   // and 512 threads, two per CU, 86 us)
   if (a.swiglu && lg <= 1 && fits(lg + 1, 1)) return RowGroups{lg + 1, kMaxThreads, 1};
+  // Permuted rows of which two workgroups of one fit a CU, but no two of two: the
+  // gather outweighs the overlap, and two rows share its column numbers (M = 4096,
+  // 4-6-8, K = 20480 96 -> 74 us, K = 28672 134 -> 105; the kernel with a table of
+  // them 80 and 143).  Not with RMS normalisation (177, 189).  All 6-bit images
+  // from the next length on (K = 14336 69 -> 62, table 65; 4-6-8 52.5, 54.5).
+  if (a.perm && !a.rmsnorm && fits(lg + 1, 1) &&
+      (lg == 0 || (lg == 1 && !a.weights && !a.write_rows && 2 * g.S[2] > g.nsteps)))
+    return RowGroups{lg + 1, kMaxThreads, 1};
   return RowGroups{lg, 64 * std::min(waves(lg), kMaxWaves / 2), 2};
 }
 

@@ -111,3 +111,24 @@ def test_silu_groups_of_one_workgroup(M, K, widths):
     qa, ea = oracle.quantize(fused.swiglu_bf16(case.a_bits, up), perm=case.perm, widths=w)
     q, E, pad_ok = decode_act(am.cpu().numpy(), ae.cpu().numpy(), w, M)
     assert np.array_equal(q, qa) and np.array_equal(E, ea) and pad_ok
+
+
+@pytest.mark.parametrize("M,K,counts", [(530, 20480, (500, 90, 50)), (515, 27648, (844, 10, 10)),
+                                        (1041, 14336, (30, 388, 30))])
+def test_long_permuted_rows(M, K, counts):
+    """Permuted rows of which two workgroups of one row fit a CU, and images of
+    mostly 6-bit blocks: one workgroup per CU with two rows, or four."""
+    say("long-rows", M, K, counts)
+    case = W.random_case(M + K, M, K, 300, counts, perm="random")
+    fmt = fmt_for(case)
+    a = to_dev_bf16(case.a_bits)
+    am, ae = mxq.quantize_act(a, fmt)
+    rows, exps = mxq.quantize_rows(a, fmt)
+    qa, ea = oracle.quantize(case.a_bits, perm=case.perm, widths=case.widths)
+    assert np.array_equal(rows.cpu().numpy(), oracle.pack_act(qa, case.widths))
+    assert np.array_equal(exps.cpu().numpy()[:, :K // 32], ea)
+    q, E, pad_ok = decode_act(am.cpu().numpy(), ae.cpu().numpy(), case.widths, M)
+    assert np.array_equal(q, qa) and np.array_equal(E, ea) and pad_ok
+    wm, we = mxq.pack_weights(to_dev_bf16(case.w_bits), fmt)
+    qw, ew = oracle.quantize(case.w_bits, perm=case.perm, widths=case.widths)
+    check_pack_w(case, {"w_mant": wm, "w_exp": we}, qw, ew, fmt)
