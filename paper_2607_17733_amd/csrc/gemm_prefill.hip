@@ -978,7 +978,7 @@ bool split_small(const GemmArgs &a, const LGeo &lg, int64_t nt, int64_t cus) {
   if (a.M <= 32) return false;
   const bool t4 = a.M > 48;
   const bool few = 16 * nt <= cus;
-  int most = std::max((t4 ? 53 : 21) + 13 * segs, few ? 100 : 0);
+  int most = std::max((t4 ? 57 : 21) + 13 * segs, few ? 100 : 0);
   // Full clamp: the split kernel restores an operand at a time in its 6-bit steps
   // (40 x 3072 x 4096 468' 11.6, 12.9; 64 x 8192 x 4096 468 22.9, 24.7, 368 23.7,
   // 19.9, all 6-bit (64 x 6144 x 4096) 28.4, 25.3; 40 x 8192 x 1024 468 19.0, 21.9,

@@ -75,8 +75,8 @@ def test_split_gemm_reads_large_weights_once():
     (33, 6336, 1000, (0, 0, 0, 198), "sym"),
     (40, 3840, 2100, (0, 120, 0, 0), "sym"),
     (40, 3968, 2100, (0, 124, 0, 0), "sym"),
-    (64, 4768, 2100, (0, 0, 75, 74), "sym"),
-    (50, 4832, 2100, (0, 0, 75, 76), "sym"),
+    (64, 5024, 2100, (0, 0, 79, 78), "sym"),
+    (50, 5120, 2100, (0, 0, 80, 80), "sym"),
     # and under the full clamp: mixed maps with and without 3-bit blocks
     (40, 1824, 2100, (0, 0, 29, 28), "full"),
     (40, 1888, 2100, (0, 0, 30, 29), "full"),
