@@ -57,6 +57,8 @@
 extern "C" {
 #endif
 
+/* Raised when an entry point that was there changes; one that was added since
+ * (mxq_calib_colsq_list) is found by its name. */
 #define MXQ_ABI_VERSION 12
 #define MXQ_BLOCK 32
 /* mxq_gemm uses the weight-streaming decode kernel up to this M (up to four
@@ -433,9 +435,10 @@ mxq_status mxq_peak_mfma(int kind, int64_t iters, float *sink, int64_t *ops,
  * where K and V are the dequantized cache values q * 2^(E - 127 - (m - 2)), for
  * every E alike: a block that held an Inf or NaN has E = 255 and zero mantissas
  * and counts as zeros (the GEMMs give NaN for it).
- * Arithmetic is float32: each block's dot product, then its scale; an
- * online softmax over chunks of 32 tokens; partial results merged in a
- * fixed order, so repeated calls give identical results.
+ * A dequantized value is exact in bf16, so each product of the two matrix
+ * products is exact and their sums are float32; an online softmax over chunks
+ * of 32 tokens; partial results merged in a fixed order, so repeated calls
+ * give identical results.
  *   fmt     the cache format: K = 128 (the head dimension), perm NULL,
  *           widths as for mxq_quantize_act (round and clamp do not matter
  *           here).

@@ -187,8 +187,6 @@ __device__ inline void load_raw(const uint8_t *row, int g, Raw<Gm> &r) {
   }
 }
 
-__device__ inline int sext(uint32_t v, int bits) { return (int)(v << (32 - bits)) >> (32 - bits); }
-
 // (a & m) | (b & ~m) for m = 0x0F0F0F0F; the mask is opaque to the compiler,
 // which would split a constant one into two instructions.
 __device__ inline uint32_t low_nibbles_else(uint32_t a, uint32_t b) {

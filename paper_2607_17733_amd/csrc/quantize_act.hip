@@ -21,8 +21,9 @@
 // per register); the mantissas are computed in fp32, where every step is
 // exact: x * 2^-s scales an 8-bit significand by a power of two, rint and the
 // clamp act on integers below 2^8.  The packed row is assembled from the
-// integers' low bytes, four elements per register.  The operand image uses the gfx950 scaled FP6/FP8 conversions (the values
-// are exact in the target format, so they never round).
+// integers' low bytes, four elements per register.  The operand image uses the
+// gfx950 scaled FP6/FP8 conversions (the values are exact in the target format,
+// so they never round).
 #include "mxq_device.h"
 #include "mxq_internal.h"
 #include <algorithm>
@@ -41,9 +42,7 @@ typedef unsigned u2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kMaxThreads = 1024;
-constexpr int kLdsBudget = 144 * 1024;  // staged rows of one workgroup per CU
 constexpr int kRowPad = 8;              // zero bf16 elements after each staged row
-constexpr int64_t kPermTableMaxK = 32767;  // 16-bit byte offsets into a staged row
 
 // A block of 32 values kept as its even and odd elements (the register
 // layout the FP6 conversion takes).
@@ -684,9 +683,9 @@ __global__ __launch_bounds__(kMaxThreads) void quantize_act_kernel(QuantArgs q) 
     constexpr int kBatch = 8;
     if (PROD != kProdSwiglu && q.vec16 && K % 512 == 0 && R * q.ld * 2 <= 0x7fffffff) {
       // Rows of whole 1 KB pieces go straight into LDS (direct-to-LDS loads,
-      // one piece per wave instruction), so no thread waits for its data
-      // before the permutation table is written.  Rows past the source's end
-      // read zeros: the buffer resource ends at its last row.
+      // one piece per wave instruction), all in flight until the wait before the
+      // barrier below.  Rows past the source's end read zeros: the buffer
+      // resource ends at its last row.
       const int64_t live = q.src_rows > r0 ? q.src_rows - r0 : 0;
       const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
           (void *)(q.src + r0 * q.ld), 0, (int)min(live * q.ld * 2, (int64_t)0x7fffffff),
