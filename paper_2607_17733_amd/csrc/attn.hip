@@ -612,7 +612,9 @@ void attn_decode_kernel(AttnArgs a) {
 // o[b][h] = the splits' partials merged in a fixed order.  Groups of LPG lanes
 // (four values each, from column 4 LPG blockIdx.z) take every kGroups-th split,
 // BATCH splits' loads in flight together, so that kGroups * BATCH splits cost
-// one memory latency; then the groups are merged in order.
+// one memory latency; then the groups are merged pairwise (one after the other
+// their rounding was the largest part of the result's: 1 x 1777 tokens 1.57e-7
+// from 64 bits, pairwise 1.35e-7).
 constexpr int kCombThreads = 256;
 
 template <int LPG, int BATCH>
@@ -667,14 +669,21 @@ __global__ __launch_bounds__(kCombThreads) void attn_combine_kernel(AttnArgs a) 
 #pragma unroll
   for (int o = 1; o < kGroups; o *= 2) Mx = fmaxf(Mx, __shfl_xor(Mx, o));
   const float w = m == ninf ? 0.f : expf(m - Mx);
-  float Ls = 0.f, Os = 0.f;
+  float Ls[kGroups], Os[kGroups];
 #pragma unroll
   for (int k = 0; k < kGroups; ++k) {
     const float f = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), k));
-    Ls += pl[k] * f;
-    Os += po[k][t] * f;
+    Ls[k] = pl[k] * f;
+    Os[k] = po[k][t] * f;
   }
-  a.o[((int64_t)b * a.Hq + h) * kD + c0 + t] = Os / Ls;
+#pragma unroll
+  for (int n = kGroups / 2; n > 0; n /= 2)
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+      Ls[k] += Ls[k + n];
+      Os[k] += Os[k + n];
+    }
+  a.o[((int64_t)b * a.Hq + h) * kD + c0 + t] = Os[0] / Ls[0];
 }
 
 template <int N3, int N4, int N6, int N8>

@@ -7,7 +7,6 @@ is no fallback: if the library is missing the calls raise ``MxqError``.
 from __future__ import annotations
 
 import ctypes
-import operator
 import os
 
 import numpy as np
@@ -142,18 +141,12 @@ class Format:
     def ref(self):
         return self._ref
 
-    def _size_of(self, count: int, tile: int, unit: int, what: str) -> int:
-        """Bytes of `count` rows or columns in whole tiles of `tile`."""
-        n = operator.index(count)
-        if n < 0:
-            _check(2, what)
-        return (n + tile - 1) // tile * self._units()[unit]
-
     def _units(self):
         """What every size is a multiple of: the bytes of a 16-row activation
         tile and its scales, a 128-column weight super-slab and its scales, a
         packed row, an exponent row.  Asked of the library once per width map:
-        a serving loop checks its buffers on every call."""
+        a serving loop checks its buffers on every call.  (The shift that counts
+        the tiles refuses a fraction.)"""
         w = self.widths.tobytes()
         if w != self._of:
             L, r = lib(), self._ref
@@ -181,17 +174,25 @@ class Format:
 
     def act_bytes(self, M: int) -> int:
         """The activation operand image of M rows (mxq_quantize_act)."""
-        return self._size_of(M, 16, 0, "mxq_act_bytes")
+        if M < 0:
+            _check(2, "mxq_act_bytes")
+        return (M + 15 >> 4) * self._units()[0]
 
     def act_exp_bytes(self, M: int) -> int:
         """Its scale bytes."""
-        return self._size_of(M, 16, 1, "mxq_act_exp_bytes")
+        if M < 0:
+            _check(2, "mxq_act_exp_bytes")
+        return (M + 15 >> 4) * self._units()[1]
 
     def weight_bytes(self, N: int) -> int:
-        return self._size_of(N, 128, 2, "mxq_weight_bytes")
+        if N < 0:
+            _check(2, "mxq_weight_bytes")
+        return (N + 127 >> 7) * self._units()[2]
 
     def weight_exp_bytes(self, N: int) -> int:
-        return self._size_of(N, 128, 3, "mxq_weight_exp_bytes")
+        if N < 0:
+            _check(2, "mxq_weight_exp_bytes")
+        return (N + 127 >> 7) * self._units()[3]
 
 
 def _bf16_2d(t, K, what):
@@ -493,12 +494,13 @@ def _colsq_list(samples):
     CALIB_LIST_MAX samples: one sample's columns fill a fraction of the GPU.
     None for samples that are not all bf16 [rows, K] of one K and device
     (they are summed one call each)."""
-    if len(samples) < 2 or not all(isinstance(x, torch.Tensor) and x.is_cuda and x.dim() == 2
-                                   and x.dtype == torch.bfloat16 and x.stride(1) == 1
-                                   and x.shape[1] == samples[0].shape[1]
-                                   and x.device == samples[0].device for x in samples):
+    first = samples[0] if len(samples) > 1 else None
+    if not (isinstance(first, torch.Tensor) and first.is_cuda and first.dim() == 2):
         return None
-    K, dev = samples[0].shape[1], samples[0].device
+    K, dev = first.shape[1], first.device
+    if not all(isinstance(x, torch.Tensor) and x.dim() == 2 and x.dtype is torch.bfloat16
+               and x.stride(1) == 1 and x.shape[1] == K and x.device == dev for x in samples):
+        return None
     s = torch.empty(K, dtype=torch.float64, device=dev)
     work = torch.empty(min(len(samples), CALIB_LIST_MAX) * K, dtype=torch.float64, device=dev)
     for i in range(0, len(samples), CALIB_LIST_MAX):
@@ -517,13 +519,12 @@ def calibrate(samples, s_layer: float, R: float, n8_blocks: int = 1):
     permutation.  Returns (perm int32 device tensor, widths list).  The first
     sample's width is the layer's: no later one may be wider (a narrower one
     counts for the columns that it has)."""
-    s = None
-    if isinstance(samples, (list, tuple)):
-        for x in samples:
-            if _sample(x, 2).shape[1] > samples[0].shape[1]:
-                raise MxqError("a calibration sample is wider than the first one")
-        s = _colsq_list(samples)
+    s = _colsq_list(samples) if isinstance(samples, (list, tuple)) else None
     if s is None:
+        if isinstance(samples, (list, tuple)):
+            for x in samples:
+                if _sample(x, 2).shape[1] > samples[0].shape[1]:
+                    raise MxqError("a calibration sample is wider than the first one")
         for i, x in enumerate(samples):
             s = calib_colsq(x, s, accumulate=i > 0)
     K = s.numel()
