@@ -42,10 +42,10 @@
 // width mix of the four blocks is its own instance, so block offsets and
 // widths are compile-time constants.
 //
-// 16 sequences, 8 KV heads, 4096 tokens, widths 4/4/6/8: 31 us (46 with a
-// per-element dequantization of V gathered byte by byte); with the merge, over
-// caches not yet read, all 4-bit 26.1 (39.9), all 8-bit 43.1 (46.0), all 3-bit
-// 30.5 (140).
+// 16 sequences, 8 KV heads, 4096 tokens, with the merge, over caches not yet
+// read (with a per-element dequantization of V gathered byte by byte): widths
+// 4/4/6/8 40.4 us (49.6), all 4-bit 32.7 (40.6), all 8-bit 44.1 (47.1), all
+// 3-bit 32.6 (142).
 #include <algorithm>
 #include <mutex>
 
