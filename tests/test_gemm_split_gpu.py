@@ -21,7 +21,7 @@ SHAPES = [
     (33, 256, 16, (0, 0, 8, 0), "rna"),
     (64, 320, 300, (0, 0, 0, 10), "full"),
     (20, 256, 8321, (0, 4, 2, 2), "sym"),      # at most 32 rows, 66 column tiles
-    (16, 256, 24449, (0, 4, 2, 2), "sym"),     # at most 16 rows, 192 column tiles
+    (16, 256, 24449, (0, 4, 2, 2), "sym"),     # at most 16 rows over short K: streamed
     (257, 256, 3700, (0, 4, 2, 2), "sym"),     # four shares of 64 rows
     (300, 640, 3500, (5, 7, 5, 3), "full"),
     (600, 256, 4500, (0, 4, 2, 2), "sym"),     # two shares of 64 rows
